@@ -171,10 +171,13 @@ __device__ inline uint32_t lds_addr_of(const void* p) { return (uint32_t)(uintpt
 // clobber keeps LDS accesses on their side.  M0 is an input operand of the
 // statement ("{m0}" constraint): the compiler writes it right before the
 // load and knows it holds the LDS address, so none of its own uses of M0 can
-// be disturbed.  The s_nop gives the one wait state between that M0 write
-// and the load that reads it.
+// be disturbed.  The s_nop gives five wait states: a vector-memory instruction
+// must not read a scalar register earlier than that after a VALU instruction
+// wrote it (sbase usually comes from v_readfirstlane, or from a spill by
+// v_readlane), and the compiler does not see into the statement; it also
+// covers the one wait state between the M0 write and the load that reads it.
 __device__ inline void lds_dma_asm(uint32_t m0, uint64_t sbase, uint32_t voff) {
-    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "{m0}"(m0) : "memory");
+    asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "{m0}"(m0) : "memory");
 }
 
 __device__ inline void lds_dma16(uint32_t lds_addr, const void* sbase, uint32_t voff) {

@@ -12,7 +12,11 @@ kernels exactly as the build does and walk the generated assembly:
   * no accumulator is copied between AGPRs (v_accvgpr_mov), which the
     compiler only does when it moves a value it does not see being written.
 
-The walker is checked on a small synthetic listing first."""
+  * no vector-memory instruction reads a scalar register within five wait
+    states of a VALU instruction writing it (the LDS-DMA loads are inline
+    assembly too, and their base address comes through v_readfirstlane).
+
+The walkers are checked on small synthetic listings first."""
 import os
 import re
 import subprocess
@@ -120,4 +124,54 @@ def test_attention_kernel_assembly(src, tmp_path):
     text = out.read_text()
     assert "v_mfma" in text
     found = hazards(text)
+    assert not found, found[:10]
+
+
+def scalar_base_hazards(asm_text):
+    """(line, wait states, text) of every vector-memory instruction that reads a scalar register fewer
+    than five wait states after a VALU instruction wrote it.  Lines are taken in listing order."""
+    found, age = [], {}
+    for k, line in enumerate(asm_text.split("\n")):
+        op, ops = _split(line)
+        if not op or op.endswith(":") or op.startswith((".", ";")):
+            continue
+        if op.startswith(("global_", "buffer_", "flat_", "scratch_")):
+            for o in ops:
+                m = re.match(r"^s\[(\d+):(\d+)\]$", o.split()[0]) if o else None
+                for r in range(int(m.group(1)), int(m.group(2)) + 1) if m else ():
+                    if age.get(r, 99) < 5:
+                        found.append((k, age[r], line.strip()))
+        step = int(ops[0], 0) + 1 if op == "s_nop" else 1
+        age = {r: a + step for r, a in age.items() if a + step < 5}
+        dst = ops[0] if ops else ""
+        m = re.match(r"^s(?:(\d+)|\[(\d+):(\d+)\])$", dst)
+        if m and op.startswith("v_"):
+            lo = int(m.group(1) or m.group(2))
+            for r in range(lo, int(m.group(3) or lo) + 1):
+                age[r] = 0
+        elif m:
+            lo = int(m.group(1) or m.group(2))
+            for r in range(lo, int(m.group(3) or lo) + 1):
+                age.pop(r, None)
+    return found
+
+
+def test_walker_flags_early_scalar_reads():
+    load = "\tglobal_load_lds_dwordx4 v5, s[4:5]\n"
+    assert scalar_base_hazards("\tv_readfirstlane_b32 s4, v2\n\ts_mov_b32 m0, s7\n\ts_nop 0\n" + load)
+    assert scalar_base_hazards("\tv_readlane_b32 s5, v254, 34\n\ts_nop 3\n" + load)
+    assert not scalar_base_hazards("\tv_readfirstlane_b32 s4, v2\n\ts_nop 4\n" + load)
+    assert not scalar_base_hazards("\tv_readfirstlane_b32 s6, v2\n" + load)      # another register
+    assert not scalar_base_hazards("\tv_readfirstlane_b32 s4, v2\n\ts_mov_b32 s4, s8\n" + load)
+
+
+@pytest.mark.parametrize("src", sorted(f for f in os.listdir(B.CSRC) if f.startswith("attn_") and f.endswith(".hip")))
+def test_loads_wait_for_their_scalar_base(src, tmp_path):
+    out = tmp_path / (src + ".s")
+    cmd = [B.hipcc()] + B.compile_flags() + B.FILE_FLAGS.get(src, []) + [
+        "--cuda-device-only", "-S", os.path.join(B.CSRC, src), "-o", str(out)]
+    subprocess.run(cmd, check=True, capture_output=True)
+    text = out.read_text()
+    assert "global_load_lds" in text
+    found = scalar_base_hazards(text)
     assert not found, found[:10]
