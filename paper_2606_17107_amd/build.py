@@ -42,6 +42,8 @@ def compile_flags():
 # for all MFMA builtins of a function.
 FILE_FLAGS = {
     "attn_mla_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "attn_gqa_rows.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "attn_mla_rows.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 
 

@@ -309,6 +309,7 @@ pkv_status check_attention(const void* q, const void* k, const void* v, void* ou
     a.max_q = d->cu_q ? d->max_q : d->total_q;
     a.max_kv_len = d->max_kv_len;
     a.n_splits = d->n_splits;
+    a.auto_splits = d->n_splits == 0;
     a.window = d->window;
     a.cache_slots = d->cache_slots;
     a.scale = scale;
@@ -516,6 +517,7 @@ PKV_EXPORT pkv_status pkv_suffix_attention_noalloc(const void* q, const void* k_
                         splits, need, (size_t)PKV_NOALLOC_SCRATCH_BYTES);
         while (splits > 1 && pkv::attention_workspace_bytes(a, splits) > PKV_NOALLOC_SCRATCH_BYTES) --splits;
         need = pkv::attention_workspace_bytes(a, splits);
+        a.auto_splits = 0;   // fewer records than the plan of the library's choice needs
     }
     a.n_splits = splits;
     if (need > 0) {

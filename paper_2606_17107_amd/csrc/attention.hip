@@ -2,12 +2,16 @@
 // (Paper Sec. 5 "Linear-time TTFT": the transplant costs a re-rotation pass
 // plus the causal attention of the suffix over the spliced cache.)
 // The bf16 GQA kernel lives in attn_gqa_bf16.hip.
-#include "attn_common.h"
+#include <algorithm>
+
+#include "attn_columns.h"
 
 namespace pkv {
 
 hipError_t launch_attn_gqa_bf16(const AttnArgs& a, const Plan& p, dim3 grid, hipStream_t stream);
 hipError_t launch_attn_mla_bf16(const AttnArgs& a, const Plan& p, dim3 grid, hipStream_t stream);
+hipError_t launch_attn_gqa_rows(const AttnArgs& a, const ColPlan& p, dim3 grid, hipStream_t stream);
+hipError_t launch_attn_mla_rows(const AttnArgs& a, const ColPlan& p, dim3 grid, hipStream_t stream);
 
 namespace {
 
@@ -198,24 +202,33 @@ __global__ __launch_bounds__(128) void attn_gqa_f32(AttnArgs a, Plan p) {
 }
 
 // Merge split-KV partials: out = sum_s w_s O_s / sum_s w_s with
-// w_s = 2^(lse_s - max lse).  Grid (row tiles, sequences from seq0, layers);
-// a thread takes kCombineCV 16-byte chunks of one (query, head) output row,
-// so its index arithmetic (32-bit) and log-sum-exp loads serve several
-// chunks.  Rows that no sequence owns (outside every cu_q range) are left
-// untouched, as the one-pass kernels leave them.
-constexpr int kCombineCV = 2;   // 16-byte output chunks per thread
-constexpr int kCombineCB = 8;   // splits whose partials are loaded in one batch
+// w_s = 2^(lse_s - max lse).  Grid (row tiles, sequences from seq0, layers).
+// With few rows the pass is latency-bound: the split partials of one row are
+// dealt to SG groups of threads, one 16-byte chunk of the row per thread, so that
+// a thread loads few records and the whole GPU takes part; the groups are merged
+// in LDS.  With many rows (SG 1) it is bound by the stream of partials and a
+// thread takes two chunks.  Rows that no sequence owns (outside every cu_q range) are
+// left untouched, as the one-pass kernels leave them.  COLUMNS: the partials of
+// the few-row kernels, which write a varying number of records per row (the
+// rest have log-sum-exp -inf and are not read) and mark rows that need no merge.
+template <int SG, bool COLUMNS>
 __global__ __launch_bounds__(256) void attn_combine(AttnArgs a, int seq0) {
-    constexpr int CV = kCombineCV, CB = kCombineCB;
+    constexpr int CB = SG == 1 ? 8 : 4;   // records loaded in one batch
+    constexpr int CV = SG == 1 ? 2 : 1;   // 16-byte chunks per thread
+    __shared__ f32x4 acc_lds[SG > 1 ? 256 : 1];
+    __shared__ float max_lds[SG > 1 ? 256 : 1], sum_lds[SG > 1 ? 256 : 1];
     const int dv = a.head_dim_v;
     const int64_t items = (int64_t)a.n_layers * a.total_q * a.n_heads;   // partial records per split
-    const uint32_t per_item = (uint32_t)dv / (4 * CV);                  // threads per (query, head)
-    const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
-    const uint32_t rh = idx / per_item;
-    const int c0 = (int)(idx - rh * per_item) * CV;                      // first chunk of this thread
+    const uint32_t chunks = (uint32_t)dv / (4 * CV);                    // threads per (query, head) and group
+    const uint32_t per_block = 256u / (chunks * SG);                    // rows per block
+    const uint32_t t = threadIdx.x;
+    const uint32_t rl = t / (chunks * SG);
+    const uint32_t rest = t - rl * (chunks * SG);
+    const uint32_t sg = rest / chunks;
+    const int c0 = (int)(rest - sg * chunks) * CV;
+    const uint32_t rh = blockIdx.x * per_block + rl;
     const uint32_t qi = rh / (uint32_t)a.n_heads;
     const int head = (int)(rh - qi * (uint32_t)a.n_heads);
-    if (qi >= (uint32_t)a.max_q) return;
     const int seq = seq0 + (int)blockIdx.y;
     const int layer = (int)blockIdx.z;
     int q0 = 0, nq = a.total_q;
@@ -224,51 +237,73 @@ __global__ __launch_bounds__(256) void attn_combine(AttnArgs a, int seq0) {
         nq = a.cu_q[seq + 1] - q0;
     }
     if (q0 < 0 || nq < 0 || (int64_t)q0 + nq > a.total_q) nq = 0;   // as seq_info
-    if ((int)qi >= nq) return;
+    const bool mine = rl < per_block && qi < (uint32_t)a.max_q && (int)qi < nq;
     const int64_t row = q0 + (int)qi;
-    const int64_t item = ((int64_t)layer * a.total_q + row) * a.n_heads + head;
-    // The log-sum-exps and partial outputs of up to CB splits are loaded in
-    // one batch (independent loads: one memory round trip), then weighted by
-    // w_s = 2^(lse_s - max) and summed in split order; a later batch (more
-    // than CB splits) rescales the sums to its larger maximum.
+    const int64_t item = mine ? ((int64_t)layer * a.total_q + row) * a.n_heads + head : 0;
+    // Records sg, sg + SG, ..: CB at a time, loaded in one batch (one memory
+    // round trip), weighted by w_s = 2^(lse_s - max) and summed in order; a
+    // later batch rescales the sums to its larger maximum.
     const int ns = a.n_splits;
     float mx = -INFINITY, wsum = 0.f;
     f32x4 acc[CV];
 #pragma unroll
     for (int k = 0; k < CV; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int s0 = 0; s0 < ns; s0 += CB) {
-        float l[CB];
-        f32x4 v[CB][CV];
+    const float first_lse = COLUMNS && mine ? a.ws_lse[item] : 0.f;
+    if (mine) {
+        for (int s0 = (int)sg; s0 < ns; s0 += SG * CB) {
+            float l[CB];
+            f32x4 v[CB][CV];
 #pragma unroll
-        for (int j = 0; j < CB; ++j) {
-            const bool in = s0 + j < ns;
-            l[j] = in ? a.ws_lse[(int64_t)(s0 + j) * items + item] : -INFINITY;
-            const float* src = a.ws_o + ((int64_t)(s0 + j) * items + item) * dv + c0 * 4;
+            for (int j = 0; j < CB; ++j) l[j] = s0 + j * SG < ns ? a.ws_lse[(int64_t)(s0 + j * SG) * items + item] : -INFINITY;
+            if (COLUMNS && first_lse == INFINITY) break;   // the few-row kernel wrote the row itself
 #pragma unroll
-            for (int k = 0; k < CV; ++k) v[j][k] = in ? *(const f32x4*)(src + k * 4) : f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-        float bm = -INFINITY;
+            for (int j = 0; j < CB; ++j) {
+                const bool in = COLUMNS ? l[j] != -INFINITY : s0 + j * SG < ns;
+                const float* src = a.ws_o + ((int64_t)(s0 + j * SG) * items + item) * dv + c0 * 4;
 #pragma unroll
-        for (int j = 0; j < CB; ++j) bm = fmaxf(bm, l[j]);
-        if (bm == -INFINITY) continue;
-        if (bm > mx) {
-            if (mx != -INFINITY) {
-                const float r = __builtin_amdgcn_exp2f(mx - bm);
-#pragma unroll
-                for (int k = 0; k < CV; ++k) acc[k] *= r;
-                wsum *= r;
+                for (int k = 0; k < CV; ++k) v[j][k] = in ? *(const f32x4*)(src + k * 4) : f32x4{0.f, 0.f, 0.f, 0.f};
             }
-            mx = bm;
-        }
+            float bm = l[0];
 #pragma unroll
-        for (int j = 0; j < CB; ++j) {
-            if (l[j] == -INFINITY) continue;
-            const float w = __builtin_amdgcn_exp2f(l[j] - mx);
+            for (int j = 1; j < CB; ++j) bm = fmaxf(bm, l[j]);
+            if (bm == -INFINITY) continue;
+            if (bm > mx) {
+                if (mx != -INFINITY) {
+                    const float r = __builtin_amdgcn_exp2f(mx - bm);
 #pragma unroll
-            for (int k = 0; k < CV; ++k) acc[k] += w * v[j][k];
-            wsum += w;
+                    for (int k = 0; k < CV; ++k) acc[k] *= r;
+                    wsum *= r;
+                }
+                mx = bm;
+            }
+#pragma unroll
+            for (int j = 0; j < CB; ++j) {
+                if (l[j] == -INFINITY) continue;
+                const float w = __builtin_amdgcn_exp2f(l[j] - mx);
+#pragma unroll
+                for (int k = 0; k < CV; ++k) acc[k] += w * v[j][k];
+                wsum += w;
+            }
         }
     }
+    if constexpr (SG > 1) {
+        acc_lds[t] = acc[0];
+        max_lds[t] = mx;
+        sum_lds[t] = wsum;
+        __syncthreads();
+        if (sg != 0) return;
+        for (int k = 1; k < SG; ++k) {
+            const float m2 = max_lds[t + k * chunks];
+            if (m2 == -INFINITY) continue;
+            const float m_new = fmaxf(mx, m2);
+            const float r1 = mx == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mx - m_new);
+            const float r2 = __builtin_amdgcn_exp2f(m2 - m_new);
+            acc[0] = acc[0] * r1 + acc_lds[t + k * chunks] * r2;
+            wsum = wsum * r1 + sum_lds[t + k * chunks] * r2;
+            mx = m_new;
+        }
+    }
+    if (!mine || (COLUMNS && first_lse == INFINITY)) return;
     const float inv = wsum > 0.f ? 1.f / wsum : 0.f;
     const int64_t oofs = (int64_t)layer * a.o_stride[0] + row * a.o_stride[1] + (int64_t)head * a.o_stride[2] + c0 * 4;
 #pragma unroll
@@ -321,9 +356,38 @@ int wgs_per_cu(const AttnArgs& a, const Plan& p) {
     return n < 1 ? 1 : (n > 2 ? 2 : n);               // two waves per SIMD at most (registers)
 }
 
+// ---- few query rows (attn_columns.h) -----------------------------------------
+
+// Rows (queries x heads per KV head) of one sequence up to which the few-row
+// kernels run: one row block.  Above it the many-row kernels are faster, since
+// they stage a tile once for 128 rows (GQA, 64 queries x 4 heads over 8256 keys:
+// 44 us with 32-row blocks, 27.5 us with 128-row ones; MLA, 16 sequences of 32
+// rows over 16384 keys: 95 us with two 16-row blocks, 74 us).
+constexpr int kRowsGqa = 32;
+constexpr int kRowsMla = 16;
+
+int64_t col_items(const AttnArgs& a) { return (int64_t)a.n_layers * a.n_kv_heads * a.n_seqs; }
+
+bool col_route(const AttnArgs& a) {
+    if (!a.auto_splits || a.dtype != 0 || a.n_seqs > kColMaxSeqs) return false;
+    const int64_t rows = (int64_t)a.max_q * (a.n_heads / a.n_kv_heads);
+    if (rows < 1 || rows > (a.variant == 1 ? kRowsMla : kRowsGqa)) return false;
+    // axis positions and workgroup ids are 32-bit
+    return col_items(a) * ((int64_t)a.max_kv_len / kColTile + 16) < 0x7fffffff;
+}
+
 }  // namespace
 
 int attention_splits(const AttnArgs& a) {
+    if (a.n_splits == 0 && a.n_seqs > 1 && col_route(a)) {
+        // Many items: whole ones (the last round is a small part of the call).
+        // Otherwise columns, with records for twice the pieces that sequences
+        // of one length would be cut into (a sequence longer than that makes
+        // the columns longer).
+        const int64_t items = col_items(a);
+        if (items >= 8 * kCUs) return 1;
+        return (int)std::min<int64_t>(32, 2 * ((kCUs + items - 1) / items) + 2);
+    }
     if (a.n_splits > 0) {
         int s = a.n_splits;
         const int max_s = (a.max_kv_len + 63) / 64;
@@ -378,13 +442,73 @@ size_t attention_workspace_bytes(const AttnArgs& a, int n_splits) {
     return rows * a.head_dim_v * sizeof(float) + rows * sizeof(float);
 }
 
+namespace {
+
+template <int SG, bool COLUMNS>
+hipError_t launch_combine_groups(const AttnArgs& a, hipStream_t stream) {
+    const int per_block = 256 / (a.head_dim_v / (SG == 1 ? 8 : 4) * SG);
+    const int64_t blocks = ((int64_t)a.max_q * a.n_heads + per_block - 1) / per_block;
+    if (blocks > 0x7fffffff || a.n_layers > 65535) return hipErrorInvalidValue;
+    // One (row tiles, sequences, layers) grid per 65535 sequences.
+    for (int seq0 = 0; seq0 < a.n_seqs; seq0 += 65535) {
+        const int nseq = a.n_seqs - seq0 < 65535 ? a.n_seqs - seq0 : 65535;
+        hipLaunchKernelGGL((attn_combine<SG, COLUMNS>), dim3((unsigned)blocks, (unsigned)nseq, (unsigned)a.n_layers),
+                           dim3(256), 0, stream, a, seq0);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// Split groups per row: one while the rows alone give four blocks a CU (the MLA
+// layer: 2048 rows of 512 channels, 16 splits, 13 us), more below that (one 8B
+// layer: 2048 rows of 128 channels, 16 splits, 6.2 us with one group, 5.7 us
+// with four), within a block of 256 threads.
+hipError_t launch_combine(const AttnArgs& a, bool columns, hipStream_t stream) {
+    if (a.max_q == 0 || a.n_layers == 0 || a.n_seqs == 0) return hipSuccess;
+    const int chunks = a.head_dim_v / 4;
+    if (a.head_dim_v % 4 || chunks > 256 || 256 % chunks) return hipErrorInvalidValue;
+    const int64_t threads = (int64_t)a.max_q * a.n_heads * a.n_layers * a.n_seqs * chunks;
+    int sg = 1;
+    while (sg < 4 && threads * sg < 4 * 256 * (int64_t)kCUs && sg * 4 < a.n_splits && sg * 2 * chunks <= 256) sg *= 2;
+    if (columns)
+        return sg == 1   ? launch_combine_groups<1, true>(a, stream)
+               : sg == 2 ? launch_combine_groups<2, true>(a, stream)
+                         : launch_combine_groups<4, true>(a, stream);
+    return sg == 1   ? launch_combine_groups<1, false>(a, stream)
+           : sg == 2 ? launch_combine_groups<2, false>(a, stream)
+                     : launch_combine_groups<4, false>(a, stream);
+}
+
+hipError_t launch_columns(const AttnArgs& a, hipStream_t stream) {
+    ColPlan p;
+    p.G = a.n_heads / a.n_kv_heads;
+    p.streams = a.n_layers * a.n_kv_heads;
+    p.pieces = a.n_splits;
+    p.columns = p.pieces > 1 ? kCUs : 0;   // one workgroup per CU (its tiles fill the LDS)
+    // Measured costs of a column's shortest useful run and of starting an item
+    // (set-up, first loads and merge: about 7 us), in tiles of one workgroup.
+    p.min_tiles = a.variant == 1 ? 4 : 8;
+    p.item_cost = a.variant == 1 ? 4 : 12;
+    const int64_t cols = p.columns ? p.columns : (col_items(a) + kXcds - 1) / kXcds * kXcds;
+    if (cols > 0x7fffffff) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)cols);
+    const hipError_t e = a.variant == 1 ? launch_attn_mla_rows(a, p, grid, stream)
+                                        : launch_attn_gqa_rows(a, p, grid, stream);
+    if (e != hipSuccess || p.columns == 0) return e;
+    return launch_combine(a, true, stream);
+}
+
+}  // namespace
+
 hipError_t launch_attention(const AttnArgs& a, hipStream_t stream) {
+    if (col_route(a)) return launch_columns(a, stream);
     const Plan p = make_plan(a, a.n_splits < 1 ? 1 : a.n_splits);
     const int64_t groups_padded = ((int64_t)p.n_groups + kXcds - 1) / kXcds * kXcds;
     const int64_t n_wg = groups_padded * p.rbs;
     if (n_wg <= 0) return hipSuccess;
     if (n_wg > 0x7fffffff) return hipErrorInvalidValue;
-    dim3 grid((unsigned)n_wg), block(256);   // the bf16 launchers set their own block size
+    dim3 grid((unsigned)n_wg);
     hipError_t e;
     if (a.dtype == 1) {
         if (a.head_dim == 64)
@@ -396,18 +520,7 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t stream) {
         e = a.variant == 1 ? launch_attn_mla_bf16(a, p, grid, stream) : launch_attn_gqa_bf16(a, p, grid, stream);
     }
     if (e != hipSuccess || p.splits == 1) return e;
-    // One (row tiles, sequences, layers) grid per 65535 sequences.
-    const int64_t threads = (int64_t)a.max_q * a.n_heads * (a.head_dim_v / (4 * kCombineCV));
-    if (threads == 0 || a.n_layers == 0 || a.n_seqs == 0) return hipSuccess;
-    if (a.head_dim_v % (4 * kCombineCV) || threads > 0xffffffffLL || a.n_layers > 65535) return hipErrorInvalidValue;
-    for (int seq0 = 0; seq0 < a.n_seqs; seq0 += 65535) {
-        const int nseq = a.n_seqs - seq0 < 65535 ? a.n_seqs - seq0 : 65535;
-        dim3 cgrid((unsigned)((threads + 255) / 256), (unsigned)nseq, (unsigned)a.n_layers);
-        hipLaunchKernelGGL(attn_combine, cgrid, block, 0, stream, a, seq0);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    return launch_combine(a, false, stream);
 }
 
 }  // namespace pkv

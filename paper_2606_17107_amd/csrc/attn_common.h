@@ -36,6 +36,16 @@ struct Plan {
     int qb, nw, ns; // bf16 GQA kernel shape: 32-row blocks per wave, waves, LDS stages
 };
 
+// Plan of the few-row kernels (attn_columns.h).
+struct ColPlan {
+    int G;            // query heads per KV head
+    int streams;      // layers x KV heads
+    int columns;      // a multiple of the XCD count; 0: one workgroup per whole item
+    int pieces;       // most pieces of one item (records the workspace has per row); 1: columns is 0
+    int min_tiles;    // shortest column
+    int item_cost;    // starting an item, in tiles
+};
+
 // Workgroup id -> (group, row block).  Workgroups are dispatched round-robin
 // over the 8 XCDs by id; giving every row block of a group (which all read the
 // same K/V range) an id with the same residue mod 8 keeps them on one XCD, at

@@ -20,7 +20,7 @@
 //     16-key step ordered as the P^T accumulator holds them.
 #include <type_traits>
 
-#include "attn_common.h"
+#include "attn_gqa_tile.h"
 
 namespace pkv {
 namespace {
@@ -32,29 +32,6 @@ constexpr int kQB = 1;       // 32-row blocks per wave
 constexpr int kWaves = 4;
 constexpr int kStages = 4;
 constexpr int kAhead = 3;    // LDS operand reads issued this many operands ahead of their MFMA
-
-// XOR swizzles of a row's 16-byte chunk index by its key.  LDS has 64 banks
-// of 4 bytes (256 bytes per cycle); the rows one read touches must spread
-// over the 16 bank groups of 16 bytes.
-//   D = 128 (16 chunks per row, every row starting at bank 0):
-//     K tiles: an operand read takes one logical chunk from 16 consecutive
-//     keys, so the swizzle is a bijection of key & 15.
-//     V tiles: a transposed read takes a 4-chunk window from 4 consecutive
-//     keys, so bits 2..3 follow key & 3; depending on key & 7 only, it is the
-//     same for keys 8 apart, which keeps their reads one immediate apart.
-//     (Measured: K reads conflict free; V reads at the transposed-read rate.)
-//   D = 64 (8 chunks per row, rows alternating between bank halves): keys of
-//     one parity share a half, 3 bits suffice for both.
-template <int D>
-__device__ inline int swz_k(int key) {
-    if constexpr (D == 128) return ((key & 3) << 2) | ((key >> 2) & 3);
-    else return ((key & 3) << 1) | ((key >> 2) & 1);
-}
-template <int D>
-__device__ inline int swz_v(int key) {
-    if constexpr (D == 128) return (key & 3) << 2;
-    else return ((key & 3) << 1) | ((key >> 2) & 1);
-}
 
 template <int D, bool PAGED>
 __global__ __launch_bounds__(kWaves * 64, 2) void attn_gqa_bf16_kernel(AttnArgs a, Plan p) {
@@ -219,34 +196,13 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_gqa_bf16_kernel(AttnArgs 
         }
     };
 
-    // Per-lane LDS element offsets of the MFMA operands within a stage.  The
-    // K swizzle depends only on key & 15 and the V swizzle on key & 7, the same
-    // for a lane's K reads of every key block and its V reads of every 8 keys,
-    // so those strides are immediates:
-    //   K (A of S^T = K Q^T), k-step ks, key block kb: kofs[ks] + kb * 32 * D
-    //   V^T (A of O^T = V^T P^T), 16-key step st, half b, channel block db:
-    //       vofs[db] + (st * 16 + b * 8) * D
     int kofs[KS], vofs[DB];
-    {
-        const int sk = swz_k<D>(j);
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) kofs[ks] = j * D + (((ks * 2 + hl) ^ sk) << 3);
-        const int g = lane >> 4, sl = lane & 15;
-        const int vkey = (g >> 1) * 4 + (sl >> 2);   // key within its group of 8
-        const int sv = swz_v<D>(vkey);
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-            vofs[db] = vkey * D + (((db * 4 + (g & 1) * 2 + ((sl & 3) >> 1)) ^ sv) << 3) + (sl & 1) * 4;
-    }
+    gqa_operand_offsets<D>(lane, kofs, vofs);
     auto k_operand = [&](const uint16_t* ks_src, int ks, int kb) __attribute__((always_inline)) {
         return __builtin_bit_cast(bf16x8, *(const u32x4*)(ks_src + kofs[ks] + kb * 32 * D));
     };
     auto v_operand = [&](const uint16_t* vs_src, int st, int db) __attribute__((always_inline)) {
-        const uint16_t* base = vs_src + vofs[db] + st * 16 * D;
-        const s16x4 p0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(PKV_LDS(s16x4, base));
-        const s16x4 p1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(PKV_LDS(s16x4, base + 8 * D));
-        return __builtin_bit_cast(bf16x8, (short __attribute__((ext_vector_type(8)))){p0[0], p0[1], p0[2], p0[3],
-                                                                                       p1[0], p1[1], p1[2], p1[3]});
+        return gqa_v_operand<D>(vs_src + vofs[db] + st * 16 * D);
     };
 
     f32x16 o[DB][QB];

@@ -42,7 +42,7 @@
 //     row's exact maximum, known from the first pass, as the reference.
 #include <type_traits>
 
-#include "attn_common.h"
+#include "attn_mla_tile.h"
 
 namespace pkv {
 namespace {
@@ -50,21 +50,6 @@ namespace {
 constexpr int kMlaWaves = 4;    // 32 rows per wave, 128 per workgroup
 constexpr int kMlaStages = 2;   // LDS stages of 32-key tiles
 constexpr int kMlaAhead = 2;    // LDS operand reads issued this many operands ahead of their MFMA
-
-constexpr int MBN = 32;        // keys per tile
-constexpr int DQK = 576;       // score channels
-constexpr int DV = 512;        // value (latent) channels
-constexpr int MCH = DQK / 8;   // 16-byte chunks per row: 72
-
-// XOR swizzle of the low three bits of a row's 16-byte chunk index by its key.
-// A row is 72 chunks, so consecutive keys start in alternate halves of the 16
-// bank groups (16 bytes each).  K operand reads take one chunk from each of 16
-// consecutive keys: for either key parity the swizzle is a bijection of
-// (key >> 1) & 7, so the 16 reads hit 16 groups.  Transposed V reads take a
-// 4-chunk aligned window from each of 4 consecutive keys: keys 4q and 4q+2
-// (and 4q+1, 4q+3) differ in bit 2 of the swizzle, which moves the window to
-// the other half of its 8-chunk group.
-__device__ inline int mswz(int key) { return (((key >> 1) & 1) << 2) | ((key >> 2) & 3); }
 
 template <bool PAGED>
 __global__ __launch_bounds__(kMlaWaves * 64, 1) void attn_mla_bf16_kernel(AttnArgs a, Plan p) {

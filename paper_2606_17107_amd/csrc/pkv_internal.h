@@ -88,6 +88,7 @@ struct AttnArgs {
     int32_t max_q;
     int32_t max_kv_len;
     int32_t n_splits;
+    int32_t auto_splits;      // n_splits is the library's own choice (the few-row kernels are eligible)
     int32_t window;           // 0: full causal; W > 0: slots j > q_pos - W only
     int64_t cache_slots;
     float scale;

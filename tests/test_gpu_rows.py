@@ -1,0 +1,88 @@
+"""GPU parity of the few-row attention kernels (token-by-token generation and
+very short suffixes: at most 32 rows per KV head, 16 for MLA) against the fp64
+oracle, at the edges of their partition: one sequence and 64, lengths around
+the 32-key tile, sequences with no queries or no slots, one sequence far longer
+than the rest (cut into the most pieces the workspace holds), more items than
+columns, row counts 1 to the limit and one past it (the many-row kernel),
+windows, paged pools and positions in no order.  Bars as elsewhere: max-abs
+2e-2, mean-abs 2e-3, relative L2 1e-2; log-sum-exp 2e-2."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from helpers import Guarded, bits_to_f64, check_attention_close, host_bits, log
+from paper_2606_17107_amd import pkv, synth
+
+pytestmark = pytest.mark.gpu
+
+CASES = {
+    "one query, one sequence": dict(H=32, Hkv=8, d=128, nq=[1], kv=[1500]),
+    "tile edges": dict(H=8, Hkv=2, d=128, nq=[1] * 7, kv=[1, 31, 32, 33, 64, 65, 255]),
+    "head size 64, 7 heads a group": dict(H=14, Hkv=2, d=64, nq=[2, 4, 1], kv=[700, 90, 3000]),
+    "32 rows": dict(H=8, Hkv=2, d=128, nq=[8, 8], kv=[900, 40]),
+    "33 rows (many-row kernel)": dict(H=3, Hkv=1, d=128, nq=[11, 11], kv=[900, 40]),
+    "no queries, no slots": dict(H=8, Hkv=2, d=128, nq=[0, 1, 2, 0, 1], kv=[50, 0, 200, 300, 77]),
+    "one long sequence": dict(H=4, Hkv=2, d=128, nq=[1] * 6, kv=[9000, 5, 5, 5, 5, 5]),
+    "64 sequences, two layers": dict(H=8, Hkv=4, d=64, nq=[1] * 64, kv=[20 + 37 * (i % 11) for i in range(64)], L=2),
+    "more items than columns": dict(H=8, Hkv=8, d=64, nq=[1] * 64, kv=[30 + i for i in range(64)], L=4),
+    "window": dict(H=8, Hkv=2, d=128, nq=[3, 1, 2], kv=[800, 33, 2000], window=100),
+    "positions in no order": dict(H=8, Hkv=2, d=128, nq=[6, 4], kv=[500, 900], pos=[-1, 0, 31, 32, 499, 600, 5, 899, 64, 320]),
+    "paged": dict(H=8, Hkv=2, d=128, nq=[1, 2, 1], kv=[1000, 65, 3000], page=32),
+    "MLA": dict(H=16, Hkv=1, d=576, nq=[1] * 5, kv=[1, 33, 700, 5000, 64]),
+    "MLA, 8 heads, two queries": dict(H=8, Hkv=1, d=576, nq=[2, 1, 0, 2], kv=[300, 40, 9, 1111]),
+    "MLA, paged, window": dict(H=16, Hkv=1, d=576, nq=[1, 1], kv=[600, 2100], page=64, window=333),
+    "MLA, 24 rows (many-row kernel)": dict(H=8, Hkv=1, d=576, nq=[3], kv=[500]),
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_few_rows(name):
+    c = CASES[name]
+    H, Hkv, d, L, nq, kv = c["H"], c["Hkv"], c["d"], c.get("L", 1), c["nq"], c["kv"]
+    mla, page, window = d == 576, c.get("page", 0), c.get("window", 0)
+    dv, n, rows = 512 if mla else d, len(nq), sum(nq)
+    scale = 1 / math.sqrt(192 if mla else d)
+    log("few rows:", name)
+    g = synth.Draws(77, "cuda")
+    q = g.normal((L, rows, H, d))
+    q_pos = c.get("pos") or [kv[s] - nq[s] + i for s in range(n) for i in range(nq[s])]
+    cu = np.concatenate([[0], np.cumsum(nq)]).astype(np.int32)
+    base = np.concatenate([[0], np.cumsum(kv)]).astype(np.int64)
+    out = Guarded((L, rows, H, dv), torch.bfloat16)
+    lse = torch.zeros(L, rows, H, dtype=torch.float32, device="cuda")
+    args = dict(n_seqs=n, cu_q=torch.from_numpy(cu).cuda(), max_q=max(nq), lse_out=lse, window=window,
+                variant=pkv.PKV_ATTN_MLA if mla else pkv.PKV_ATTN_GQA)
+    pos_d = torch.tensor(q_pos, dtype=torch.int32, device="cuda")
+    kv_d = torch.tensor(kv, dtype=torch.int32, device="cuda")
+    if page:
+        per = -(-max(kv) // page)
+        table = torch.randperm(per * n + 3, generator=g.gen, device="cuda")[: per * n].to(torch.int32).view(n, per)
+        k = g.normal((L, per * n + 3, page, Hkv, d))
+        v = k[..., :512] if mla else g.normal((L, per * n + 3, page, Hkv, dv))
+        pkv.suffix_attention_paged(q, k, v, out.t, pos_d, kv_d, table.contiguous(), scale, max(kv), **args)
+        flat = lambda t, l, s: t[l, table[s].long()].reshape(per * page, Hkv, -1).transpose(0, 1)[:, : kv[s]]
+    else:
+        k = g.normal((L, Hkv, int(base[-1]), d))
+        v = k[..., :512] if mla else g.normal((L, Hkv, int(base[-1]), dv))
+        pkv.suffix_attention(q, k, v, out.t, pos_d, kv_d, scale, max(kv), kv_base=torch.from_numpy(base[:n]).cuda(),
+                             **args)
+        flat = lambda t, l, s: t[l, :, base[s]: base[s] + kv[s]]
+    torch.cuda.synchronize()
+    out.check("few-row attention output")
+    got, got_lse, qh = host_bits(out.t), lse.cpu().numpy(), host_bits(q)
+    want, want_lse = np.zeros((L, rows, H, dv)), np.full((L, rows, H), -np.inf)
+    for l in range(L):
+        for s in range(n):
+            if nq[s] and kv[s]:
+                r = slice(cu[s], cu[s + 1])
+                want[l, r], want_lse[l, r] = oracle.attention(
+                    np.ascontiguousarray(qh[l, r]), host_bits(flat(k, l, s).contiguous()),
+                    host_bits(flat(v, l, s).contiguous()), np.asarray(q_pos[r], np.int32), kv[s], scale, window=window)
+    empty = np.isneginf(want_lse)
+    assert np.array_equal(np.isneginf(got_lse), empty) and np.all(got[empty] == 0)
+    np.testing.assert_allclose(got_lse[~empty], want_lse[~empty], atol=2e-2)
+    # one bf16 ulp of outputs of size 4 (few visible keys) is 2^-6; elsewhere the bar of the other tests
+    log("  ", check_attention_close(got, want, max_abs=2e-2 if np.abs(want).max() < 2.5 else 2 ** -5))
