@@ -344,6 +344,7 @@ Plan make_plan(const AttnArgs& a, int splits) {
     if (p.rbs < 1) p.rbs = 1;
     p.splits = splits;
     p.n_groups = a.n_layers * a.n_kv_heads * a.n_seqs * splits;
+    p.longest_first = 0;
     return p;
 }
 
@@ -503,11 +504,14 @@ hipError_t launch_columns(const AttnArgs& a, hipStream_t stream) {
 
 hipError_t launch_attention(const AttnArgs& a, hipStream_t stream) {
     if (col_route(a)) return launch_columns(a, stream);
-    const Plan p = make_plan(a, a.n_splits < 1 ? 1 : a.n_splits);
+    Plan p = make_plan(a, a.n_splits < 1 ? 1 : a.n_splits);
     const int64_t groups_padded = ((int64_t)p.n_groups + kXcds - 1) / kXcds * kXcds;
     const int64_t n_wg = groups_padded * p.rbs;
     if (n_wg <= 0) return hipSuccess;
     if (n_wg > 0x7fffffff) return hipErrorInvalidValue;
+    // More workgroups than the CUs hold at once (bf16 GQA): the order matters.
+    p.longest_first = a.dtype == 0 && a.variant == 0 && a.n_seqs > 1 && a.n_seqs <= 64 &&
+                      n_wg > kCUs * (int64_t)wgs_per_cu(a, p);
     dim3 grid((unsigned)n_wg);
     hipError_t e;
     if (a.dtype == 1) {

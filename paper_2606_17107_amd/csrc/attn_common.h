@@ -33,6 +33,7 @@ struct Plan {
     int rbs;        // row blocks per group
     int n_groups;   // layers x kv heads x sequences x splits
     int splits;     // each workgroup's key range is shared by this many splits in equal runs of whole tiles
+    int longest_first;   // sequences are dispatched longest first
     int qb, nw, ns; // bf16 GQA kernel shape: 32-row blocks per wave, waves, LDS stages
 };
 
@@ -57,6 +58,23 @@ __device__ inline bool decode(const Plan& p, int& group, int& rb) {
     rb = slot % p.rbs;
     group = (slot / p.rbs) * kXcds + xcd;
     return group < p.n_groups;
+}
+
+// The index-th longest sequence (by cache length, ties by number).  Sequences are
+// dispatched longest first when there are more workgroups than slots, so that
+// the last round holds the shortest (16 caches of 8448..12544 keys, 256 queries
+// each, 1024 workgroups for 512 slots: 695 us in the given order, 664 us).
+// n_seqs <= 64: lane s ranks sequence s.
+__device__ inline int longest_seq(const AttnArgs& a, int index) {
+    const int s = (int)__lane_id();
+    const int len = s < a.n_seqs ? a.kv_len[s] : -1;
+    int rank = 0;
+    for (int t = 0; t < a.n_seqs; ++t) {
+        const int other = __builtin_amdgcn_readlane(len, t);
+        rank += other > len || (other == len && t < s);
+    }
+    const uint64_t at = __builtin_amdgcn_ballot_w64(s < a.n_seqs && rank == index);
+    return at ? __builtin_ctzll(at) : index;
 }
 
 struct SeqInfo {

@@ -63,7 +63,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_gqa_bf16_kernel(AttnArgs 
     const int kvh = rest % a.n_kv_heads;
     rest /= a.n_kv_heads;
     const int layer = rest % a.n_layers;
-    const int seq = rest / a.n_layers;
+    int seq = rest / a.n_layers;
+    if (p.longest_first) seq = longest_seq(a, seq);
     const SeqInfo si = seq_info(a, seq);
     const int M = si.nq * p.G;
     const int m0 = rb * (NW * 32 * QB);
