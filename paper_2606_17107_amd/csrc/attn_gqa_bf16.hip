@@ -88,25 +88,25 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_gqa_bf16_kernel(AttnArgs 
         qi[qb] = row_ok[qb] ? m / p.G : 0;
         head[qb] = kvh * p.G + (row_ok[qb] ? m - qi[qb] * p.G : 0);
     }
-    // Q^T B operands: 8 channels of the row per k-step (loaded first: they do not
-    // depend on the positions, so their latency overlaps the key-range set-up).
+    // Positions, then the Q^T B operands (8 channels of the row per k-step): the
+    // key-range set-up needs the positions only, so the Q loads stay in flight
+    // over it.  Rows past M repeat row 0 (never written).
+    int pos[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) pos[qb] = a.q_pos[si.q0 + qi[qb]];
     bf16x8 qf[QB][KS];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         const uint16_t* qrow = (const uint16_t*)a.q + (int64_t)layer * a.q_stride[0] +
                                (int64_t)(si.q0 + qi[qb]) * a.q_stride[1] + (int64_t)head[qb] * a.q_stride[2];
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if (row_ok[qb]) v = *(const u32x4*)(qrow + ks * 16 + hl * 8);
-            qf[qb][ks] = __builtin_bit_cast(bf16x8, v);
-        }
+        for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qrow + ks * 16 + hl * 8));
     }
 
     int rmax = 0, rmin = 0x7fffffff, smin = 0x7fffffff, smax = 0;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-        const int qpos = row_ok[qb] ? a.q_pos[si.q0 + qi[qb]] : -1;
+        const int qpos = row_ok[qb] ? pos[qb] : -1;
         visible_range(qpos, si.kvl, a.window, row_start[qb], row_end[qb]);   // (0, 0) for rows past M
         rmax = max(rmax, row_end[qb]);
         if (row_ok[qb]) {
