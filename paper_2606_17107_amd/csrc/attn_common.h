@@ -32,6 +32,7 @@ struct Plan {
     int BM;         // rows per workgroup
     int rbs;        // row blocks per group
     int n_groups;   // layers x kv heads x sequences x splits
+    int shares, share_rbs;   // XCDs that share a group, row blocks of one share
     int splits;     // each workgroup's key range is shared by this many splits in equal runs of whole tiles
     int longest_first;   // sequences are dispatched longest first
     int qb, nw, ns; // bf16 GQA kernel shape: 32-row blocks per wave, waves, LDS stages
@@ -50,14 +51,16 @@ struct ColPlan {
 // Workgroup id -> (group, row block).  Workgroups are dispatched round-robin
 // over the 8 XCDs by id; giving every row block of a group (which all read the
 // same K/V range) an id with the same residue mod 8 keeps them on one XCD, at
-// consecutive dispatch slots, so they share that XCD's L2.
+// consecutive dispatch slots, so they share that XCD's L2.  Where the groups do
+// not fill the XCDs evenly, a group's row blocks are dealt to p.shares XCDs.
 __device__ inline bool decode(const Plan& p, int& group, int& rb) {
     const int id = blockIdx.x;
     const int xcd = id % kXcds;
     const int slot = id / kXcds;
-    rb = slot % p.rbs;
-    group = (slot / p.rbs) * kXcds + xcd;
-    return group < p.n_groups;
+    const int share = (slot / p.share_rbs) * kXcds + xcd;
+    group = share / p.shares;
+    rb = (share - group * p.shares) * p.share_rbs + slot % p.share_rbs;
+    return group < p.n_groups && rb < p.rbs;
 }
 
 // The index-th longest sequence (by cache length, ties by number).  Sequences are

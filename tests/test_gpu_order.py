@@ -1,4 +1,4 @@
-"""Ragged sequences in the many-row GQA kernel when its workgroups outnumber the
+"""Dispatch order of the many-row attention kernels.  Ragged sequences in the GQA kernel when its workgroups outnumber the
 slots of the GPU, where sequences are dispatched longest first: ascending,
 equal and zero lengths, 2 and 64 sequences, and 65 (the order given), against
 the fp64 oracle (max-abs 2e-2, mean-abs 2e-3, relative L2 1e-2)."""
@@ -41,3 +41,31 @@ def test_longest_first(n, nq, L, d):
             want.append(oracle.attention(np.ascontiguousarray(qh[l, r]), np.ascontiguousarray(kh[l][:, c]),
                                          np.ascontiguousarray(vh[l][:, c]), q_pos[r], kv[s], 1 / math.sqrt(d))[0])
         check_attention_close(got[l], np.concatenate(want))
+
+
+@pytest.mark.parametrize("variant,H,Hkv,d,nq,splits", [
+    ("gqa", 8, 1, 64, 150, 1),      # 1 group, 10 row blocks: shared by 8 XCDs
+    ("gqa", 8, 2, 128, 97, 3),      # 6 groups, 4 row blocks
+    ("gqa", 12, 3, 128, 33, 1),     # 3 groups, 2 row blocks: more XCDs than row blocks
+    ("gqa", 20, 5, 64, 300, 1),     # 5 groups, 10 row blocks
+    ("mla", 16, 1, 576, 70, 3),     # 3 groups, 9 row blocks
+    ("f32", 6, 3, 64, 130, 1),      # 3 groups, 5 row blocks of 64
+])
+def test_row_blocks_shared_by_xcds(variant, H, Hkv, d, nq, splits):
+    """Group counts that do not divide over the XCDs: every row block is dealt to exactly one workgroup."""
+    log("shared groups:", variant, H, Hkv, nq, splits)
+    mla, dt = variant == "mla", torch.float32 if variant == "f32" else torch.bfloat16
+    kv, dv = 700, 512 if mla else d
+    scale = 1 / math.sqrt(192 if mla else d)
+    g = synth.Draws(300 + H + nq, "cuda")
+    q, k = g.normal((1, nq, H, d), dt), g.normal((1, Hkv, kv, d), dt)
+    v = k[..., :512] if mla else g.normal((1, Hkv, kv, d), dt)
+    out = Guarded((1, nq, H, dv), dt)
+    q_pos = np.arange(kv - nq, kv, dtype=np.int32)
+    pkv.suffix_attention(q, k, v, out.t, torch.from_numpy(q_pos).cuda(), torch.tensor([kv], dtype=torch.int32, device="cuda"),
+                         scale, kv, n_splits=splits, variant=pkv.PKV_ATTN_MLA if mla else pkv.PKV_ATTN_GQA)
+    torch.cuda.synchronize()
+    out.check("attention output")
+    got = host_bits(out.t)
+    want, _ = oracle.attention(host_bits(q)[0], host_bits(k)[0], host_bits(v.contiguous())[0], q_pos, kv, scale)
+    check_attention_close(got[0], want)
