@@ -201,6 +201,206 @@ __global__ __launch_bounds__(128) void attn_gqa_f32(AttnArgs a, Plan p) {
                 f32x4{o[db][4 * jj] * inv, o[db][4 * jj + 1] * inv, o[db][4 * jj + 2] * inv, o[db][4 * jj + 3] * inv};
 }
 
+// fp32 kernel for calls that do not fill the GPU: a workgroup covers 32 rows, its
+// four waves hold the same rows and split the keys (wave w takes every fourth
+// 32-key tile of the workgroup's run through its own LDS stages: no barrier in
+// the loop) and are merged in LDS at the end.  Such a call is a chain of memory
+// round trips and of one tile's 64 MFMAs after another, so the chain is what is
+// cut: 16 queries over 528 keys, 2 KV heads: 16.8 us with two row waves of which
+// one is idle and three tiles one after another, 8 us here.  Layout as above,
+// except that a score step takes channel s from one half-wave and s + D/2 from
+// the other, so a lane's query channels are contiguous; LDS rows are padded so
+// that the two halves' reads fall into different banks.
+template <int D>
+__global__ __launch_bounds__(256) void attn_gqa_f32_keys(AttnArgs a, Plan p) {
+    constexpr int BN = 32, NW = 4;
+    constexpr int KSF = D / 2;              // score steps (2 channels each)
+    constexpr int DB = D / 32;              // 32-channel output blocks
+    constexpr int NL = BN * D / 4 / 64;     // 16-byte loads per lane per tensor and tile
+    constexpr int KT = D * BN + 32;         // transposed K tile: [channel][key], the upper half 32 words on
+    constexpr int VS = D + 8;               // V row stride
+    constexpr int WAVE = KT + BN * VS;      // floats per wave
+    constexpr int OC = D / 4;               // 16-byte chunks per output row
+    static_assert(32 * D <= WAVE && KT % 4 == 0 && WAVE % 4 == 0, "a wave's O^T fits its stages");
+    __shared__ __attribute__((aligned(16))) float lds[NW * WAVE];
+    __shared__ float max_lds[NW][32], sum_lds[NW][32];
+
+    int group, rb;
+    if (!decode(p, group, rb)) return;
+    const int split = group % p.splits;
+    int rest = group / p.splits;
+    const int kvh = rest % a.n_kv_heads;
+    rest /= a.n_kv_heads;
+    const int layer = rest % a.n_layers;
+    const int seq = rest / a.n_layers;
+    const SeqInfo si = seq_info(a, seq);
+    const int M = si.nq * p.G;
+    const int m0 = rb * 32;
+    if (m0 >= M) return;
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63;
+    const int j = lane & 31;
+    const int hl = lane >> 5;
+    const int m = m0 + j;
+    const bool row_ok = m < M;
+    const int qi = row_ok ? m / p.G : 0;                       // rows past M repeat row 0 (never written)
+    const int head = kvh * p.G + (row_ok ? m - qi * p.G : 0);
+    const int pos = a.q_pos[si.q0 + qi];
+    f32x4 q4[KSF / 4];   // channels hl D/2 .. of the lane's row
+    {
+        const float* qrow = (const float*)a.q + (int64_t)layer * a.q_stride[0] +
+                            (int64_t)(si.q0 + qi) * a.q_stride[1] + (int64_t)head * a.q_stride[2] + hl * KSF;
+#pragma unroll
+        for (int i = 0; i < KSF / 4; ++i) q4[i] = *(const f32x4*)(qrow + i * 4);
+    }
+    int row_start, row_end;
+    visible_range(row_ok ? pos : -1, si.kvl, a.window, row_start, row_end);   // (0, 0) for rows past M
+    const int e_max = wave_max_u(row_end);
+    const int s_min = wave_min_u(row_ok ? row_start : 0x7fffffff);
+    const int lo = s_min == 0x7fffffff ? 0 : s_min / BN * BN;
+    const int hi = min(si.kvl, e_max);
+    const int run = hi > lo ? ((hi - lo + p.splits - 1) / p.splits + BN - 1) / BN * BN : 0;
+    const int k_begin = lo + split * run;
+    const int k_end = min(hi, k_begin + run);
+
+    const float* kbase = (const float*)a.k + (int64_t)layer * a.k_stride[0] + (int64_t)kvh * a.k_stride[1] +
+                         si.base * a.k_stride[2];
+    const float* vbase = (const float*)a.v + (int64_t)layer * a.v_stride[0] + (int64_t)kvh * a.v_stride[1] +
+                         si.base * a.v_stride[2];
+    float* const kt = lds + wave * WAVE;
+    float* const vt = kt + KT;
+    // Piece id = lane + 64 i of a tile: K key id % 32, channels 4 (id / 32) .. +3;
+    // V key id / (D/4), channels 4 (id % (D/4)) .. +3.  Keys past k_end load zeros.
+    f32x4 pk[NL], pv[NL];
+    auto load_tile = [&](int t0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int id = lane + i * 64;
+            const int kk = id % BN, kc = id / BN, vk = id / (D / 4), vc = id % (D / 4);
+            pk[i] = t0 + kk < k_end ? *(const f32x4*)(kbase + (int64_t)(t0 + kk) * a.k_stride[2] + kc * 4)
+                                    : f32x4{0.f, 0.f, 0.f, 0.f};
+            pv[i] = t0 + vk < k_end ? *(const f32x4*)(vbase + (int64_t)(t0 + vk) * a.v_stride[2] + vc * 4)
+                                    : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+
+    // A wave executes its LDS accesses in order; the compiler, which sees one
+    // lane at a time, must not move one lane's reads over another's writes.
+    auto wave_fence = []() __attribute__((always_inline)) {
+        __builtin_amdgcn_wave_barrier();
+        asm volatile("" ::: "memory");
+    };
+
+    f32x16 o[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db) o[db] = f32x16{};
+    float m_run = -INFINITY, l_run = 0.f;   // running maximum (log2 units) and sum
+    const int first = k_begin + wave * BN;
+    if (first < k_end) load_tile(first);
+#pragma unroll 1
+    for (int t0 = first; t0 < k_end; t0 += NW * BN) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int id = lane + i * 64;
+            const int kk = id % BN, kc = id / BN, vk = id / (D / 4), vc = id % (D / 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) kt[(kc * 4 + e) * BN + (kc * 4 >= KSF ? 32 : 0) + kk] = pk[i][e];
+            *(f32x4*)(vt + vk * VS + vc * 4) = pv[i];
+        }
+        wave_fence();
+        if (t0 + NW * BN < k_end) load_tile(t0 + NW * BN);
+        f32x16 sc = f32x16{};
+#pragma unroll
+        for (int s = 0; s < KSF; ++s)
+            sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kt[(s + hl * KSF) * BN + hl * 32 + j], q4[s / 4][s % 4] * a.scale,
+                                                      sc, 0, 0, 0);
+        // Element r of the lane holds key t0 + 8 (r / 4) + 4 hl + r % 4 of row j.
+        float mx = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int key = t0 + (r >> 2) * 8 + hl * 4 + (r & 3);
+            if (!(key < row_end && key >= row_start && key < k_end)) sc[r] = -INFINITY;
+            mx = fmaxf(mx, sc[r]);
+        }
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+        mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * kLog2e;
+        // Branch-free: a row that has seen no visible key keeps o = 0 and l = 0.
+        const float m_new = fmaxf(m_run, mx);
+        const float alpha = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
+        float lsum = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            // (one rounding of the exponent: the product is not rounded by itself)
+            const float e = sc[r] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(fmaf(sc[r], kLog2e, -m_new));
+            sc[r] = e;
+            lsum += e;
+        }
+        l_run = l_run * alpha + lsum;
+        m_run = m_new;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) o[db] *= alpha;
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr)
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+                    o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vt[(8 * jj + 4 * hl + rr) * VS + db * 32 + j],
+                                                                 sc[4 * jj + rr], o[db], 0, 0, 0);
+        wave_fence();
+    }
+
+    // Merge the waves: O row-major in each wave's own stages, 16-byte chunks
+    // XOR-swizzled by row.  Element 4 jj + rr of block db is channel 32 db + 8 jj + 4 hl + rr.
+    const float l_tot = l_run + __shfl_xor(l_run, 32);
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj)
+            *(f32x4*)(kt + j * D + ((db * 8 + jj * 2 + hl) ^ (j & (OC - 1))) * 4) =
+                f32x4{o[db][4 * jj], o[db][4 * jj + 1], o[db][4 * jj + 2], o[db][4 * jj + 3]};
+    if (hl == 0) {
+        max_lds[wave][j] = m_run;
+        sum_lds[wave][j] = l_tot;
+    }
+    __syncthreads();
+    const int c = tid % OC;
+#pragma unroll
+    for (int r = tid / OC; r < 32; r += 256 / OC) {
+        if (m0 + r >= M) break;
+        float mw[NW], top = -INFINITY, sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            mw[w] = max_lds[w][r];
+            top = fmaxf(top, mw[w]);
+        }
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float wt = mw[w] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw[w] - top);
+            acc += wt * *(const f32x4*)(lds + w * WAVE + r * D + (c ^ (r & (OC - 1))) * 4);
+            sum += wt * sum_lds[w][r];
+        }
+        const float inv = sum > 0.f ? 1.f / sum : 0.f;
+        const float lse2 = sum > 0.f ? top + __log2f(sum) : -INFINITY;
+        const int q = (m0 + r) / p.G;
+        const int hd = kvh * p.G + m0 + r - q * p.G;
+        const int64_t row = si.q0 + q;
+        if (p.splits == 1) {
+            *(f32x4*)((float*)a.out + (int64_t)layer * a.o_stride[0] + row * a.o_stride[1] +
+                      (int64_t)hd * a.o_stride[2] + c * 4) = acc * inv;
+            if (a.lse_out && c == 0)
+                a.lse_out[((int64_t)layer * a.total_q + row) * a.n_heads + hd] = lse2 * kLn2;
+        } else {
+            const int64_t item = (((int64_t)split * a.n_layers + layer) * a.total_q + row) * a.n_heads + hd;
+            *(f32x4*)(a.ws_o + item * D + c * 4) = acc * inv;
+            if (c == 0) a.ws_lse[item] = lse2;
+        }
+    }
+}
+
 // Merge split-KV partials: out = sum_s w_s O_s / sum_s w_s with
 // w_s = 2^(lse_s - max lse).  Grid (row tiles, sequences from seq0, layers).
 // With few rows the pass is latency-bound: the split partials of one row are
@@ -322,7 +522,8 @@ __global__ __launch_bounds__(256) void attn_combine(AttnArgs a, int seq0) {
         a.lse_out[item] = wsum > 0.f ? (mx + __log2f(wsum)) * kLn2 : -INFINITY;
 }
 
-Plan make_plan(const AttnArgs& a, int splits) {
+// rows: rows per workgroup, 0 for the dtype's usual count.
+Plan make_plan(const AttnArgs& a, int splits, int rows = 0) {
     Plan p;
     p.G = a.n_heads / a.n_kv_heads;
     const int64_t m_rows = (int64_t)a.max_q * p.G;
@@ -339,7 +540,7 @@ Plan make_plan(const AttnArgs& a, int splits) {
         p.nw = 4;
         p.ns = 4;
     }
-    p.BM = a.dtype == 1 ? 64 : p.nw * 32 * p.qb;
+    p.BM = rows ? rows : a.dtype == 1 ? 64 : p.nw * 32 * p.qb;
     p.rbs = (int)((m_rows + p.BM - 1) / p.BM);
     if (p.rbs < 1) p.rbs = 1;
     p.splits = splits;
@@ -518,6 +719,10 @@ hipError_t launch_columns(const AttnArgs& a, hipStream_t stream) {
 hipError_t launch_attention(const AttnArgs& a, hipStream_t stream) {
     if (col_route(a)) return launch_columns(a, stream);
     Plan p = make_plan(a, a.n_splits < 1 ? 1 : a.n_splits);
+    // fp32 calls of at most one workgroup of 32 rows per CU split the keys over
+    // its waves.
+    const bool keys = a.dtype == 1 && (int64_t)p.n_groups * (((int64_t)a.max_q * p.G + 31) / 32) <= kCUs;
+    if (keys) p = make_plan(a, p.splits, 32);
     const int64_t n_wg = ((int64_t)p.n_groups * p.shares + kXcds - 1) / kXcds * kXcds * p.share_rbs;
     if (n_wg <= 0) return hipSuccess;
     if (n_wg > 0x7fffffff) return hipErrorInvalidValue;
@@ -526,7 +731,13 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t stream) {
                       n_wg > kCUs * (int64_t)wgs_per_cu(a, p);
     dim3 grid((unsigned)n_wg);
     hipError_t e;
-    if (a.dtype == 1) {
+    if (keys) {
+        if (a.head_dim == 64)
+            hipLaunchKernelGGL((attn_gqa_f32_keys<64>), grid, dim3(256), 0, stream, a, p);
+        else
+            hipLaunchKernelGGL((attn_gqa_f32_keys<128>), grid, dim3(256), 0, stream, a, p);
+        e = hipGetLastError();
+    } else if (a.dtype == 1) {
         if (a.head_dim == 64)
             hipLaunchKernelGGL((attn_gqa_f32<64>), grid, dim3(128), 0, stream, a, p);
         else
