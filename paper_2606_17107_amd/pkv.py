@@ -156,6 +156,11 @@ def _keep_until_done(t: Optional[torch.Tensor], stream) -> None:
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
+        # torch's current stream on the current device, by the raw accessors once
+        # torch has initialised the GPU: current_stream() looks the device up
+        # through the environment and builds a Stream object (4 us a call).
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
     if isinstance(stream, int):
         return stream
@@ -174,7 +179,7 @@ def _need(t, name: str, device: torch.device, dtype=None, numel: Optional[int] =
         return
     if not isinstance(t, torch.Tensor):
         raise TypeError("%s must be a torch.Tensor, got %s" % (name, type(t).__name__))
-    if dtype is not None and t.dtype != dtype:
+    if dtype is not None and t.dtype is not dtype:
         raise TypeError("%s must be %s, got %s" % (name, dtype, t.dtype))
     if numel is not None and t.numel() < numel:
         raise ValueError("%s holds %d elements, the call reads %d" % (name, t.numel(), numel))
@@ -305,30 +310,20 @@ def _dtype_code(t: torch.Tensor) -> int:
 def _strides3(t: Optional[torch.Tensor]):
     if t is None:
         return _i64x3(0, 0, 0)
-    assert t.dim() == 4 and t.stride(3) == 1, "cache tensors are [layer][head][slot][channel], channels contiguous"
-    return _i64x3(t.stride(0), t.stride(1), t.stride(2))
+    st = t.stride()
+    assert len(st) == 4 and st[3] == 1, "cache tensors are [layer][head][slot][channel], channels contiguous"
+    return _i64x3(st[0], st[1], st[2])
 
 
 def make_layout(src_k: torch.Tensor, src_v: Optional[torch.Tensor], dst_k: torch.Tensor,
                 dst_v: Optional[torch.Tensor], rope_offset: int = 0, rope_style: int = PKV_ROPE_HALF,
                 n_tokens: Optional[int] = None, err_flag: Optional[torch.Tensor] = None) -> pkv_layout:
     """Layout for [layer][kv_head][slot][channel] tensors (any strides, channels contiguous)."""
-    L = pkv_layout()
-    L.dtype = _dtype_code(src_k)
-    L.n_layers, L.n_kv_heads = src_k.shape[0], src_k.shape[1]
-    L.head_dim = src_k.shape[3]
-    L.v_dim = 0 if src_v is None else src_v.shape[3]
-    L.n_tokens = src_k.shape[2] if n_tokens is None else int(n_tokens)
-    L.rope_offset = int(rope_offset)
-    L.rope_style = int(rope_style)
-    L.dst_capacity = dst_k.shape[2]
-    L.reserved = 0
-    L.src_k_stride = _strides3(src_k)
-    L.src_v_stride = _strides3(src_v)
-    L.dst_k_stride = _strides3(dst_k)
-    L.dst_v_stride = _strides3(dst_v)
-    L.err_flag = None if err_flag is None else err_flag.data_ptr()
-    return L
+    n_layers, n_kv_heads, slots, head_dim = src_k.shape
+    return pkv_layout(_dtype_code(src_k), n_layers, n_kv_heads, head_dim, 0 if src_v is None else src_v.shape[3],
+                      slots if n_tokens is None else int(n_tokens), int(rope_offset), int(rope_style),
+                      dst_k.shape[2], 0, _strides3(src_k), _strides3(src_v), _strides3(dst_k), _strides3(dst_v),
+                      None if err_flag is None else err_flag.data_ptr())
 
 
 def reposition_splice(src_k, src_v, dst_k, dst_v, src_pos, dst_pos, rope_theta, rope_dim, rope_offset=0,
@@ -378,27 +373,14 @@ def make_attn_desc(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.Tensor
                    variant: int = PKV_ATTN_GQA, n_splits: int = 0,
                    lse_out: Optional[torch.Tensor] = None, window: int = 0) -> pkv_attn_desc:
     """Descriptor for q [L][rows][H][d], caches [L][Hkv][slots][*], out [L][rows][H][dv]."""
-    d = pkv_attn_desc()
-    d.dtype = _dtype_code(q)
-    d.variant = int(variant)
-    d.n_layers = q.shape[0]
-    d.n_seqs = int(n_seqs)
-    d.head_dim_v = out.shape[3]
-    d.total_q = q.shape[1]
-    d.max_q = q.shape[1] if max_q is None else int(max_q)
-    d.max_kv_len = int(max_kv_len)
-    d.n_splits = int(n_splits)
-    d.window = int(window)
-    d.cu_q = None if cu_q is None else cu_q.data_ptr()
-    d.kv_base = None if kv_base is None else kv_base.data_ptr()
-    d.cache_slots = k_cache.shape[2]
-    assert q.stride(3) == 1 and out.stride(3) == 1
-    d.q_stride = _i64x3(q.stride(0), q.stride(1), q.stride(2))
-    d.k_stride = _strides3(k_cache)
-    d.v_stride = _strides3(v_cache)
-    d.o_stride = _i64x3(out.stride(0), out.stride(1), out.stride(2))
-    d.lse_out = None if lse_out is None else lse_out.data_ptr()
-    return d
+    n_layers, rows = q.shape[:2]
+    qs, os_ = q.stride(), out.stride()
+    assert qs[3] == 1 and os_[3] == 1
+    return pkv_attn_desc(_dtype_code(q), int(variant), n_layers, int(n_seqs), out.shape[3], rows,
+                         rows if max_q is None else int(max_q), int(max_kv_len), int(n_splits), int(window),
+                         None if cu_q is None else cu_q.data_ptr(), None if kv_base is None else kv_base.data_ptr(),
+                         k_cache.shape[2], _i64x3(*qs[:3]), _strides3(k_cache), _strides3(v_cache),
+                         _i64x3(*os_[:3]), None if lse_out is None else lse_out.data_ptr())
 
 
 def attention_workspace(desc: pkv_attn_desc, n_q_heads: int, n_kv_heads: int, head_dim: int,
