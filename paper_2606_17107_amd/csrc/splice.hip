@@ -52,8 +52,22 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kUnroll = 1;         // rows whose loads are issued before any is used
 constexpr int kRowsPerBlock = 1;   // (layer, kv_head) rows per block
 constexpr int kBlock = 256;        // threads per block
-constexpr int kSegTiles = 32;      // segment mode: token-tile blocks per (row group, segment)
-constexpr int kSegAhead = 6;       // segment mode: tiles whose loads are issued before the first store
+// Segment mode: a block copies one run of kSegRun consecutive token tiles, whose
+// loads are issued before its first store.  The call is bound by the stream of
+// writes; what matters is how close in memory the writes in flight are and how
+// many waves issue them: 16 sequences x 3 skills, 8 layers (4.0 GB), 718 us with
+// 32 blocks a segment and row that loop over tiles 32 apart, six in flight
+// (123 registers); 694 us with the rows dealt to the XCDs in turn; 678 us with
+// runs of three and no loop as well (66 registers; with a loop 727, runs of two /
+// four / five tiles 763 / 704 / 981).  Small compositions lose the blocks that had
+// one tile of six: three heads of 64 in nine sequences 20.5 -> 14.6 us.  Above
+// kSegRuns runs a segment (6144 tokens of 128 + 128 channels) the looping form
+// runs with kSegTiles blocks, so that a loose bound on the segment length does
+// not launch a grid of empty blocks.
+constexpr int kSegRun = 3;
+constexpr int kSegRuns = 128;
+constexpr int kSegTiles = 32;      // looping form: token-tile blocks per (row group, segment)
+constexpr int kSegAhead = 6;       // looping form: tiles whose loads are issued before the first store
 constexpr int kHalf = 0;
 constexpr int kWave = 64;
 constexpr int kXcds = 8;
@@ -68,7 +82,8 @@ struct Geo {
     int lanes_k, lanes_v, lanes, tok_per_block, rows_per_block;
     int rope_c0, rope_nc, n_kc, n_vc, n_rows, n_pairs;
     int xcd_tiles;          // tiles per XCD when the tile count divides by 8, else 0
-    int seg_xcd_rows;       // segment mode, 1-D grid: row groups per XCD (0: 3-D grid)
+    int seg_xcd;            // segment mode on the 1-D grid (else 3-D)
+    int seg_loop;           // segment mode: the looping form
     int seg_n, seg_tile_blocks;   // segment mode, 1-D grid: segments, tile blocks
     uint32_t lanes_magic;   // ceil(2^32 / lanes)
     double rho[7];          // theta^(-2*2^b/rope_dim), b = 0..6
@@ -200,7 +215,8 @@ __device__ inline int lane_pair(int l, int j, int half_r) {
         return j < CE / 2 ? l * (CE / 2) + j : (half_r + l) * (CE / 2) + (j - CE / 2);
 }
 
-template <int EB, int STYLE, bool SEG, bool TAB, bool PAGED>
+// SEG: 0 per-token mode, 1 segment mode with one run per block, 2 its looping form.
+template <int EB, int STYLE, int SEG, bool TAB, bool PAGED>
 __global__ __launch_bounds__(kBlock) void splice_kernel(SpliceArgs a, Geo g, FreqArg<TAB> ft) {
     static_assert(!(PAGED && SEG), "paged destinations are per-token mode only");
     constexpr int CE = 16 / EB;   // elements per 16-byte chunk = pairs per rotary lane
@@ -218,20 +234,21 @@ __global__ __launch_bounds__(kBlock) void splice_kernel(SpliceArgs a, Geo g, Fre
     // segments that read the same source chunk (a shared skill) find it in the
     // caches.  When the row groups divide evenly over the XCDs, segment mode
     // runs on a 1-D grid whose ids are dealt to the XCDs round-robin: XCD x
-    // takes row groups x*seg_xcd_rows .. one at a time, so every read of one
+    // takes row groups x, x + 8, .. one at a time, so every read of one
     // source chunk goes through one XCD's L2 and only the first reaches
-    // memory; within a row the tile blocks of one segment are consecutive, so
-    // the blocks in flight write into few destination ranges (a row's source
-    // chunks, a few MB, stay in that L2 meanwhile).
+    // memory, and the XCDs write into neighbouring rows; within a row the
+    // tile blocks of one segment are consecutive, so the blocks in flight write
+    // into few destination ranges (a row's source chunks, a few MB, stay in
+    // that L2 meanwhile).
     int grp = blockIdx.y, seg_i = 0, tile_blk = 0, tile_blocks = 1;
     if constexpr (SEG) {
-        if (g.seg_xcd_rows) {
+        if (g.seg_xcd) {
             const uint32_t id = blockIdx.x;
             const uint32_t slot = id / kXcds;
             tile_blk = (int)(slot % (uint32_t)g.seg_tile_blocks);
             const uint32_t rest = slot / (uint32_t)g.seg_tile_blocks;
             seg_i = (int)(rest % (uint32_t)g.seg_n);
-            grp = (int)(id % kXcds) * g.seg_xcd_rows + (int)(rest / (uint32_t)g.seg_n);
+            grp = (int)(rest / (uint32_t)g.seg_n) * kXcds + (int)(id % kXcds);
             tile_blocks = g.seg_tile_blocks;
         } else {
             seg_i = blockIdx.x;
@@ -246,9 +263,8 @@ __global__ __launch_bounds__(kBlock) void splice_kernel(SpliceArgs a, Geo g, Fre
     const bool in_tile = (int)tl < g.tok_per_block;
 
     // Segment mode: the whole block works on one segment, whose delta is
-    // uniform; its tiles are shared out round-robin over the blocks of the
-    // x axis, which is sized for the longest segment (capped), so short
-    // segments leave few blocks idle.
+    // uniform; its runs of tiles are shared out round-robin over the tile
+    // blocks, whose number is sized for the longest segment (capped).
     SpliceSegment sg{};
     int64_t n_tok = a.n_tokens;
     if constexpr (SEG) {
@@ -342,25 +358,27 @@ __global__ __launch_bounds__(kBlock) void splice_kernel(SpliceArgs a, Geo g, Fre
 
     if constexpr (SEG) {
         // Segment mode: one (layer, head) row per block and one delta per
-        // segment, so the coefficients are formed once.  The block's tiles
-        // (tile_blk, tile_blk + tile_blocks, ...) go kSegAhead at a time:
-        // the loads of all of them are issued before the first store, so each
-        // wave keeps kSegAhead tiles of loads in flight.  Lanes without a
-        // readable source row load nothing.
+        // segment, so the coefficients are formed once.  The block's tiles are
+        // run tile_blk, or (looping form) tile_blk, tile_blk + tile_blocks, ...
+        // AHEAD at a time.  Lanes without a readable source row load nothing.
+        constexpr int AHEAD = SEG == 1 ? kSegRun : kSegAhead;
         static_assert(kRowsPerBlock == 1, "segment mode handles one row per block");
         const char* const srow = src_t + ((int64_t)layer0 * s0 + (int64_t)head0 * s1) * EB;
         char* const drow = dst_t + ((int64_t)layer0 * d0 + (int64_t)head0 * d1) * EB;
         const int64_t delta = (int64_t)sg.dst_pos0 - (int64_t)sg.src_pos0;
+        const uint32_t tile0 = SEG == 1 ? (uint32_t)tile_blk * AHEAD : (uint32_t)tile_blk;
+        const uint32_t tile_step = SEG == 1 ? 1u : (uint32_t)tile_blocks;
+        if ((int64_t)tile0 * g.tok_per_block >= n_tok) return;   // uniform
         coefficients(delta, true);
         const bool rot = rope && delta != 0;
-        for (uint32_t step = 0;; step += kSegAhead) {
-            if ((int64_t)(tile_blk + step * tile_blocks) * g.tok_per_block >= n_tok) break;   // uniform
-            u32x4 va[kSegAhead], vb[kSegAhead];
-            int64_t dst_row[kSegAhead];
-            bool present[kSegAhead], work[kSegAhead];
+        uint32_t first = tile0;
+        do {
+            u32x4 va[AHEAD], vb[AHEAD];
+            int64_t dst_row[AHEAD];
+            bool present[AHEAD], work[AHEAD];
 #pragma unroll
-            for (int u = 0; u < kSegAhead; ++u) {
-                const int64_t t = (int64_t)(tile_blk + (step + u) * tile_blocks) * g.tok_per_block + tl;
+            for (int u = 0; u < AHEAD; ++u) {
+                const int64_t t = (int64_t)(first + u * tile_step) * g.tok_per_block + tl;
                 present[u] = in_tile && t < n_tok;
                 const int64_t src_slot = sg.src_slot0 + t;
                 const bool active = present[u] && src_slot >= 0 && src_slot < a.n_tokens;
@@ -376,7 +394,7 @@ __global__ __launch_bounds__(kBlock) void splice_kernel(SpliceArgs a, Geo g, Fre
                 }
             }
 #pragma unroll
-            for (int u = 0; u < kSegAhead; ++u) {
+            for (int u = 0; u < AHEAD; ++u) {
                 if (work[u]) {
                     if (rot) rotate_chunks<EB, STYLE>(va[u], vb[u], cs, sn);
                     char* dp = drow + dst_row[u] * EB;
@@ -385,7 +403,8 @@ __global__ __launch_bounds__(kBlock) void splice_kernel(SpliceArgs a, Geo g, Fre
                 }
                 if (present[u] && !work[u] && lane == 0 && grp == 0 && a.err_flag) atomicOr(a.err_flag, 1);
             }
-        }
+            first += AHEAD * tile_step;
+        } while (SEG == 2 && (int64_t)first * g.tok_per_block < n_tok);
         return;
     }
 
@@ -476,18 +495,20 @@ hipError_t launch_typed(const SpliceArgs& a, const Geo& g, dim3 grid, dim3 block
     if (a.dst_pages) {   // paged destination: per-token mode, theta schedule
         if (a.segs || a.omega) return hipErrorInvalidValue;
         const FreqArg<false> ft;
-        hipLaunchKernelGGL((splice_kernel<EB, STYLE, false, false, true>), grid, block, 0, st, a, g, ft);
+        hipLaunchKernelGGL((splice_kernel<EB, STYLE, 0, false, true>), grid, block, 0, st, a, g, ft);
     } else if (a.omega) {   // explicit frequencies: per-token mode
         if (a.segs) return hipErrorInvalidValue;
         FreqArg<true> ft;
         for (int i = 0; i < (1 << kPairBits); ++i) ft.w[i] = i < g.n_pairs ? a.omega[i] : 0.0;
-        hipLaunchKernelGGL((splice_kernel<EB, STYLE, false, true, false>), grid, block, 0, st, a, g, ft);
+        hipLaunchKernelGGL((splice_kernel<EB, STYLE, 0, true, false>), grid, block, 0, st, a, g, ft);
     } else {
         const FreqArg<false> ft;
-        if (a.segs)
-            hipLaunchKernelGGL((splice_kernel<EB, STYLE, true, false, false>), grid, block, 0, st, a, g, ft);
+        if (a.segs && g.seg_loop)
+            hipLaunchKernelGGL((splice_kernel<EB, STYLE, 2, false, false>), grid, block, 0, st, a, g, ft);
+        else if (a.segs)
+            hipLaunchKernelGGL((splice_kernel<EB, STYLE, 1, false, false>), grid, block, 0, st, a, g, ft);
         else
-            hipLaunchKernelGGL((splice_kernel<EB, STYLE, false, false, false>), grid, block, 0, st, a, g, ft);
+            hipLaunchKernelGGL((splice_kernel<EB, STYLE, 0, false, false>), grid, block, 0, st, a, g, ft);
     }
     return hipGetLastError();
 }
@@ -523,7 +544,9 @@ hipError_t launch_splice(const SpliceArgs& a, hipStream_t stream) {
     if (g.n_pairs > (1 << kPairBits)) return hipErrorInvalidValue;
     g.rows_per_block = g.n_rows < kRowsPerBlock ? g.n_rows : kRowsPerBlock;
     int64_t n_tiles = (tokens + g.tok_per_block - 1) / g.tok_per_block;
-    if (seg && n_tiles > kSegTiles) n_tiles = kSegTiles;   // blocks loop over a segment's tiles
+    const int64_t n_runs = (n_tiles + kSegRun - 1) / kSegRun;
+    g.seg_loop = seg && n_runs > kSegRuns;
+    if (seg) n_tiles = g.seg_loop ? kSegTiles : n_runs;
     const int64_t n_groups = (g.n_rows + g.rows_per_block - 1) / g.rows_per_block;
     if (n_tiles > 0x7fffffff || n_groups > 65535 || nz > 65535) return hipErrorInvalidConfiguration;
     // Segment mode sizes the tile axis for the longest segment, so a shorter
@@ -536,10 +559,10 @@ hipError_t launch_splice(const SpliceArgs& a, hipStream_t stream) {
     // Segment mode with row groups divisible by the XCD count: 1-D grid
     // (decoded in the kernel so that each XCD owns whole row groups).
     const int64_t seg_1d = nz * n_tiles * n_groups;
-    g.seg_xcd_rows = seg && n_groups % kXcds == 0 && seg_1d <= 0x7fffffff ? (int)(n_groups / kXcds) : 0;
+    g.seg_xcd = seg && n_groups % kXcds == 0 && seg_1d <= 0x7fffffff;
     g.seg_n = (int)nz;
     g.seg_tile_blocks = (int)n_tiles;
-    dim3 grid = seg ? (g.seg_xcd_rows ? dim3((unsigned)seg_1d, 1u, 1u)
+    dim3 grid = seg ? (g.seg_xcd ? dim3((unsigned)seg_1d, 1u, 1u)
                                       : dim3((unsigned)nz, (unsigned)n_tiles, (unsigned)n_groups))
                     : dim3((unsigned)n_tiles, (unsigned)n_groups, 1u);
     dim3 block((unsigned)kBlock);

@@ -1,0 +1,48 @@
+"""Batched splice at the edges of its partition (a block copies a run of three
+token tiles, 16 tokens each at 8 + 8 lanes a token; above 128 runs 32 blocks
+loop over a segment): segment lengths around one tile, one run and 128 runs, a bound far above the longest segment, row counts
+that do and do not divide over the XCDs, against the fp64 oracle (values
+bit-exact, keys within one bf16 ulp)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from helpers import check_rotated_keys, dev, host_bits, log
+from paper_2606_17107_amd import pkv, synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("L,H,lens,bound", [
+    (2, 4, [1, 15, 16, 17, 47, 48, 49, 96, 97], None),    # 8 rows: 1-D grid
+    (1, 3, [1, 48, 49, 0, 200], None),                    # 3 rows: 3-D grid
+    (2, 4, [48 * 128, 48 * 128 + 1, 5], None),            # 128 runs and one token more: looping blocks
+    (2, 4, [48 * 128, 5], None),                          # 128 runs, one per block
+    (1, 1, [100, 33], 1 << 20),                           # a loose bound
+])
+def test_run_edges(L, H, lens, bound):
+    d, theta = 128, 5e5
+    log("segments:", L, H, lens, bound)
+    g = synth.Draws(7 + len(lens) + H, "cpu")
+    S, gap = sum(lens), 7
+    src_k, src_v = host_bits(g.normal((L, H, S, d))), host_bits(g.normal((L, H, S, d)))
+    cap = S + gap * (len(lens) + 1)
+    dst_k, dst_v = host_bits(g.normal((L, H, cap, d))), host_bits(g.normal((L, H, cap, d)))
+    segs, slot, at = [], 0, gap
+    for i, n in enumerate(lens):
+        segs.append(dict(src_slot0=slot, dst_seq_base=0, n_tokens=n, src_pos0=1000 * i, dst_pos0=at, dst_seq_len=cap))
+        slot, at = slot + n, at + n + gap
+    gk, gv, err = dev(dst_k), dev(dst_v), torch.zeros(1, dtype=torch.int32, device="cuda")
+    pkv.reposition_splice_batched(dev(src_k), dev(src_v), gk, gv, pkv.make_segments(segs, "cuda"), len(segs),
+                                  bound or max(lens), theta, d, err_flag=err)
+    torch.cuda.synchronize()
+    assert int(err.item()) == 0
+    for sg in segs:
+        n, s = sg["n_tokens"], slice(sg["src_slot0"], sg["src_slot0"] + sg["n_tokens"])
+        if n:
+            oracle.reposition_splice(np.ascontiguousarray(src_k[:, :, s]), np.ascontiguousarray(src_v[:, :, s]), dst_k,
+                                     dst_v, np.arange(sg["src_pos0"], sg["src_pos0"] + n, dtype=np.int32),
+                                     np.arange(sg["dst_pos0"], sg["dst_pos0"] + n, dtype=np.int32), theta, d)
+    np.testing.assert_array_equal(host_bits(gv), dst_v)   # every slot no segment owns included
+    check_rotated_keys(host_bits(gk), dst_k, 0, d, synth.HALF)
