@@ -453,15 +453,21 @@ __global__ __launch_bounds__(256) void attn_combine(AttnArgs a, int seq0) {
         for (int s0 = (int)sg; s0 < ns; s0 += SG * CB) {
             float l[CB];
             f32x4 v[CB][CV];
-#pragma unroll
-            for (int j = 0; j < CB; ++j) l[j] = s0 + j * SG < ns ? a.ws_lse[(int64_t)(s0 + j * SG) * items + item] : -INFINITY;
-            if (COLUMNS && first_lse == INFINITY) break;   // the few-row kernel wrote the row itself
-#pragma unroll
-            for (int j = 0; j < CB; ++j) {
-                const bool in = COLUMNS ? l[j] != -INFINITY : s0 + j * SG < ns;
+            auto load_part = [&](int j, bool in) __attribute__((always_inline)) {
                 const float* src = a.ws_o + ((int64_t)(s0 + j * SG) * items + item) * dv + c0 * 4;
 #pragma unroll
                 for (int k = 0; k < CV; ++k) v[j][k] = in ? *(const f32x4*)(src + k * 4) : f32x4{0.f, 0.f, 0.f, 0.f};
+            };
+#pragma unroll
+            for (int j = 0; j < CB; ++j) {
+                const bool in = s0 + j * SG < ns;
+                l[j] = in ? a.ws_lse[(int64_t)(s0 + j * SG) * items + item] : -INFINITY;
+                if (!COLUMNS) load_part(j, in);
+            }
+            if (COLUMNS && first_lse == INFINITY) break;   // the few-row kernel wrote the row itself
+            if (COLUMNS) {
+#pragma unroll
+                for (int j = 0; j < CB; ++j) load_part(j, l[j] != -INFINITY);
             }
             float bm = l[0];
 #pragma unroll
