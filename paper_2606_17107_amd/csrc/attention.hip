@@ -207,7 +207,7 @@ __global__ __launch_bounds__(128) void attn_gqa_f32(AttnArgs a, Plan p) {
 // the loop) and are merged in LDS at the end.  Such a call is a chain of memory
 // round trips and of one tile's 64 MFMAs after another, so the chain is what is
 // cut: 16 queries over 528 keys, 2 KV heads: 16.8 us with two row waves of which
-// one is idle and three tiles one after another, 8 us here.  Layout as above,
+// one is idle and three tiles one after another, 10.2 us here.  Layout as above,
 // except that a score step takes channel s from one half-wave and s + D/2 from
 // the other, so a lane's query channels are contiguous; LDS rows are padded so
 // that the two halves' reads fall into different banks.
