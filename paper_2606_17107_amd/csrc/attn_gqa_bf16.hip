@@ -211,10 +211,12 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_gqa_bf16_kernel(AttnArgs 
     for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) o[db][qb] = f32x16{};
+    // The reference maxima start below every finite score but finite, so that a
+    // tile whose scores are all -inf has weights exp2(-inf) = 0, not exp2(-inf + inf).
     float m_run[QB], l_run[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-        m_run[qb] = -INFINITY;
+        m_run[qb] = -__FLT_MAX__;
         l_run[qb] = 0.f;
     }
     const float sc2 = a.scale * kLog2e;
@@ -279,7 +281,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_gqa_bf16_kernel(AttnArgs 
             const bool up = msc > m_run[qb] + kLazy;
             if (__builtin_amdgcn_ballot_w64(up) != 0) {
                 const float m_new = up ? msc : m_run[qb];
-                const float alpha = m_run[qb] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run[qb] - m_new);
+                const float alpha = __builtin_amdgcn_exp2f(m_run[qb] - m_new);
                 l_run[qb] *= alpha;
 #pragma unroll
                 for (int db = 0; db < DB; ++db) o[db][qb] *= alpha;
@@ -295,7 +297,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_gqa_bf16_kernel(AttnArgs 
         constexpr bool MASK = decltype(mask_tag)::value;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            const float neg_m = m_run[qb] == -INFINITY ? 0.f : -m_run[qb];
+            const float neg_m = -m_run[qb];
             float lsum = 0.f;
 #pragma unroll
             for (int kb = 0; kb < NKB; ++kb) {
@@ -525,7 +527,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_gqa_bf16_kernel(AttnArgs 
                 const bool up = msc > m_run[qb] + kLazy;
                 if (__builtin_amdgcn_ballot_w64(up) != 0) {
                     const float m_new = up ? msc : m_run[qb];
-                    const float alpha = m_run[qb] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run[qb] - m_new);
+                    const float alpha = __builtin_amdgcn_exp2f(m_run[qb] - m_new);
                     l_run[qb] *= alpha;
 #pragma unroll
                     for (int db = 0; db < DB; ++db) o[db][qb] *= alpha;
