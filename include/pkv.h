@@ -266,7 +266,8 @@ typedef struct pkv_attn_desc {
     int64_t v_stride[3];    /* kernels address the keys of one tile by 32-bit byte offsets) */
     int64_t o_stride[3];
     float* lse_out;         /* optional device fp32 [n_layers][total_q][n_q_heads]: natural-log
-                               log-sum-exp of the visible scaled scores (-inf for an empty row) */
+                               log-sum-exp of the visible scaled scores (-inf for an empty row, NaN
+                               for a row that sees a NaN score or one of +inf) */
 } pkv_attn_desc;
 
 /* Bytes of device workspace pkv_suffix_attention needs for `desc` (split-KV

@@ -178,8 +178,8 @@ __global__ __launch_bounds__(128) void attn_gqa_f32(AttnArgs a, Plan p) {
     // The two halves of a row hold disjoint keys.
     const float l_tot = l_run + __shfl_xor(l_run, 32);
     if (!row_ok) return;
-    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-    const float lse2 = l_tot > 0.f ? m_run + __log2f(l_tot) : -INFINITY;
+    const float inv = row_inverse(l_tot);
+    const float lse2 = row_lse2(m_run, l_tot);
     const int64_t row = si.q0 + qi;
     // Element 4 jj + rr of block db holds channel 32 db + 8 jj + 4 hl + rr of the row.
     float* dst;
@@ -383,8 +383,8 @@ __global__ __launch_bounds__(256) void attn_gqa_f32_keys(AttnArgs a, Plan p) {
             acc += wt * *(const f32x4*)(lds + w * WAVE + r * D + (c ^ (r & (OC - 1))) * 4);
             sum += wt * sum_lds[w][r];
         }
-        const float inv = sum > 0.f ? 1.f / sum : 0.f;
-        const float lse2 = sum > 0.f ? top + __log2f(sum) : -INFINITY;
+        const float inv = row_inverse(sum);
+        const float lse2 = row_lse2(top, sum);
         const int q = (m0 + r) / p.G;
         const int hd = kvh * p.G + m0 + r - q * p.G;
         const int64_t row = si.q0 + q;
@@ -469,10 +469,15 @@ __global__ __launch_bounds__(256) void attn_combine(AttnArgs a, int seq0) {
 #pragma unroll
                 for (int j = 0; j < CB; ++j) load_part(j, l[j] != -INFINITY);
             }
+            // (fmaxf passes over a NaN: a batch whose only records are NaN has bm -inf)
             float bm = l[0];
+            bool any = l[0] != -INFINITY;
 #pragma unroll
-            for (int j = 1; j < CB; ++j) bm = fmaxf(bm, l[j]);
-            if (bm == -INFINITY) continue;
+            for (int j = 1; j < CB; ++j) {
+                bm = fmaxf(bm, l[j]);
+                any |= l[j] != -INFINITY;
+            }
+            if (!any) continue;
             if (bm > mx) {
                 if (mx != -INFINITY) {
                     const float r = __builtin_amdgcn_exp2f(mx - bm);
@@ -499,18 +504,18 @@ __global__ __launch_bounds__(256) void attn_combine(AttnArgs a, int seq0) {
         __syncthreads();
         if (sg != 0) return;
         for (int k = 1; k < SG; ++k) {
-            const float m2 = max_lds[t + k * chunks];
-            if (m2 == -INFINITY) continue;
+            const float m2 = max_lds[t + k * chunks], sum2 = sum_lds[t + k * chunks];
+            if (sum2 == 0.f) continue;   // no record (NaN records have a NaN sum and a maximum of -inf)
             const float m_new = fmaxf(mx, m2);
             const float r1 = mx == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mx - m_new);
             const float r2 = __builtin_amdgcn_exp2f(m2 - m_new);
             acc[0] = acc[0] * r1 + acc_lds[t + k * chunks] * r2;
-            wsum = wsum * r1 + sum_lds[t + k * chunks] * r2;
+            wsum = wsum * r1 + sum2 * r2;
             mx = m_new;
         }
     }
     if (!mine || (COLUMNS && first_lse == INFINITY)) return;
-    const float inv = wsum > 0.f ? 1.f / wsum : 0.f;
+    const float inv = row_inverse(wsum);
     const int64_t oofs = (int64_t)layer * a.o_stride[0] + row * a.o_stride[1] + (int64_t)head * a.o_stride[2] + c0 * 4;
 #pragma unroll
     for (int k = 0; k < CV; ++k) {
@@ -525,7 +530,7 @@ __global__ __launch_bounds__(256) void attn_combine(AttnArgs a, int seq0) {
         }
     }
     if (a.lse_out && c0 == 0)
-        a.lse_out[item] = wsum > 0.f ? (mx + __log2f(wsum)) * kLn2 : -INFINITY;
+        a.lse_out[item] = row_lse2(mx, wsum) * kLn2;
 }
 
 // rows: rows per workgroup, 0 for the dtype's usual count.

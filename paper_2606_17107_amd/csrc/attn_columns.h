@@ -196,8 +196,8 @@ __device__ __forceinline__ void col_merge_rows(const AttnArgs& a, const ColPlan&
             acc += wt * *(const f32x4*)(o_lds + w * wave_stride + r * DV + (c ^ (r & (OC - 1))) * 4);
             sum += wt * sum_lds[w * ROWS + r];
         }
-        const float inv = sum > 0.f ? 1.f / sum : 0.f;
-        const float lse2 = sum > 0.f ? mx + __log2f(sum) : -INFINITY;
+        const float inv = row_inverse(sum);
+        const float lse2 = row_lse2(mx, sum);
         const int q = r / G;
         const int head = head0 + r - q * G;
         const int64_t row = si.q0 + q;

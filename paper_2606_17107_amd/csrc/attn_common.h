@@ -180,6 +180,14 @@ __device__ inline uint32_t bf_rne(float f) {
     return u >> 16;
 }
 
+// 1 / (sum of a row's softmax weights) and its log2-sum-exp over the reference
+// ref.  The sum is 0 only for a row without a visible key, whose output is zeros
+// and whose log-sum-exp, -inf, marks a partial that weighs nothing.  The sum of a
+// row with a NaN or +inf score is NaN, and so are both results: such a partial
+// reaches the merged row instead of passing for an empty one.
+__device__ inline float row_inverse(float sum) { return sum == 0.f ? 0.f : 1.f / sum; }
+__device__ inline float row_lse2(float ref, float sum) { return sum == 0.f ? -INFINITY : ref + __log2f(sum); }
+
 // A wave-uniform 64-bit value in scalar registers.  readfirstlane returns a
 // signed int: each half is taken as uint32_t before widening.
 __device__ inline uint64_t uniform_u64(uint64_t v) {

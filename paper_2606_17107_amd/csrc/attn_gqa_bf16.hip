@@ -652,8 +652,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_gqa_bf16_kernel(AttnArgs 
     for (int qb = 0; qb < QB; ++qb) {
         const float l_tot = l_run[qb] + __shfl_xor(l_run[qb], 32);
         if (!row_ok[qb]) continue;
-        const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-        const float lse2 = l_tot > 0.f ? m_run[qb] + __log2f(l_tot) : -INFINITY;
+        const float inv = row_inverse(l_tot);
+        const float lse2 = row_lse2(m_run[qb], l_tot);
         const int64_t row = si.q0 + qi[qb];
         if (p.splits == 1) {
             uint16_t* orow = (uint16_t*)a.out + (int64_t)layer * a.o_stride[0] + row * a.o_stride[1] +

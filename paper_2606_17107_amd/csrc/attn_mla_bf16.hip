@@ -393,8 +393,8 @@ __global__ __launch_bounds__(kMlaWaves * 64, 1) void attn_mla_bf16_kernel(AttnAr
 
     const float l_tot = l_run + __shfl_xor(l_run, 32);
     if (!row_ok) return;
-    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-    const float lse2 = l_tot > 0.f ? m_run + __log2f(l_tot) : -INFINITY;
+    const float inv = row_inverse(l_tot);
+    const float lse2 = row_lse2(m_run, l_tot);
     const int64_t row = si.q0 + qi;
     if (p.splits == 1) {
         uint16_t* orow = (uint16_t*)a.out + (int64_t)layer * a.o_stride[0] + row * a.o_stride[1] +

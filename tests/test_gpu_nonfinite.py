@@ -1,8 +1,10 @@
-"""Infinities through every attention kernel and both merges of partials, against
-a float64 softmax: keys whose score is -inf weigh nothing, also where they fill
-whole tiles or splits, and the other rows are as close as elsewhere (max-abs 2e-2;
-1e-5 in fp32).  "few": the library's choice of splits, for calls of few rows;
-"many": the same work with splits given, which runs the many-row kernels."""
+"""NaN and infinities through every attention kernel and both merges of partials,
+against a float64 softmax: a row that sees a NaN score or one of +inf is NaN in
+the output and in the log-sum-exp, a NaN in one value channel stays in that
+channel, keys whose score is -inf weigh nothing, and the other KV head's rows are
+as close as elsewhere (max-abs 2e-2; 1e-5 in fp32).  "few": the library's choice
+of splits, for calls of few rows; "many": the same work with splits given, which
+runs the many-row kernels."""
 import math
 
 import numpy as np
@@ -31,7 +33,9 @@ ROUTES = {   # variant, query heads, KV heads, head size, queries, cache lengths
     "fp32, rows, 3 splits": ("f32", 8, 8, 64, 1100, [1200], 3),
 }
 # what is planted: first and last key (of the first sequence, KV head 0), channel, value
-PLANTS = {"-inf scores": (0, 64, 0, -math.inf), "-inf scores, half": (0, 0.5, 0, -math.inf)}
+PLANTS = {"NaN key": (100, 101, 0, math.nan), "NaN keys": (0, None, 0, math.nan), "+inf score": (100, 101, 0, math.inf),
+          "-inf scores": (0, 64, 0, -math.inf), "-inf scores, half": (0, 0.5, 0, -math.inf),
+          "NaN value": (100, 101, None, math.nan)}
 
 
 @pytest.mark.parametrize("plant", PLANTS)
