@@ -252,15 +252,12 @@ __global__ __launch_bounds__(kRowWaves * 64, 2) void attn_gqa_rows_kernel(AttnAr
                 m_run = m_new;
             }
             const float neg_m = m_run == -INFINITY ? 0.f : -m_run;
-            float lsum = 0.f;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 float e = __builtin_amdgcn_exp2f(fmaf(s[r], sc2, neg_m));
                 if (MASK && hidden(r)) e = 0.f;
                 s[r] = e;
-                lsum += e;
             }
-            l_run += lsum;
 #pragma unroll
             for (int st = 0; st < 2; ++st) {
                 f32x8 pv;
@@ -268,6 +265,14 @@ __global__ __launch_bounds__(kRowWaves * 64, 2) void attn_gqa_rows_kernel(AttnAr
                 for (int e = 0; e < 8; ++e) pv[e] = s[st * 8 + e];
                 pb[st] = __builtin_convertvector(pv, bf16x8);
             }
+            // The row sum takes the probabilities as they enter PV, rounded to bf16, as in
+            // the many-row kernel: the rounding of a key that dominates its row cancels.
+            const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+            float lsum = 0.f;
+#pragma unroll
+            for (int e = 0; e < 16; e += 2)
+                lsum = __builtin_amdgcn_fdot2_f32_bf16((bf16x2){pb[e >> 3][e & 7], pb[e >> 3][(e & 7) + 1]}, ones, lsum, false);
+            l_run += lsum;
         };
         auto add_values = [&](const uint16_t* vs_src, const bf16x8 (&pb)[2]) __attribute__((always_inline)) {
 #pragma unroll
