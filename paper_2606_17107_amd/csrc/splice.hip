@@ -217,7 +217,7 @@ __device__ inline int lane_pair(int l, int j, int half_r) {
 
 // SEG: 0 per-token mode, 1 segment mode with one run per block, 2 its looping form.
 template <int EB, int STYLE, int SEG, bool TAB, bool PAGED>
-__global__ __launch_bounds__(kBlock) void splice_kernel(SpliceArgs a, Geo g, FreqArg<TAB> ft) {
+__global__ __launch_bounds__(kBlock, SEG == 1 ? 5 : 1) void splice_kernel(SpliceArgs a, Geo g, FreqArg<TAB> ft) {
     static_assert(!(PAGED && SEG), "paged destinations are per-token mode only");
     constexpr int CE = 16 / EB;   // elements per 16-byte chunk = pairs per rotary lane
     // Explicit frequencies: lane l holds those of pairs l and 64 + l, loaded
@@ -405,6 +405,28 @@ __global__ __launch_bounds__(kBlock) void splice_kernel(SpliceArgs a, Geo g, Fre
             }
             first += AHEAD * tile_step;
         } while (SEG == 2 && (int64_t)first * g.tok_per_block < n_tok);
+        // The runs cover the stated bound on the segment lengths; the tiles of a
+        // segment beyond it are dealt to the blocks in turn, one at a time.  (Runs
+        // in a loop instead take 78 registers: one wave a SIMD less for every call.)
+        if constexpr (SEG == 1) {
+            for (uint32_t tile = (uint32_t)(tile_blocks * AHEAD + tile_blk); (int64_t)tile * g.tok_per_block < n_tok;
+                 tile += (uint32_t)tile_blocks) {
+                const int64_t t = (int64_t)tile * g.tok_per_block + tl;
+                if (!in_tile || t >= n_tok) continue;
+                const int64_t src_slot = sg.src_slot0 + t, p = (int64_t)sg.dst_pos0 + t;
+                const int64_t dst_slot = p >= 0 && p < sg.dst_seq_len ? sg.dst_seq_base + p : -1;
+                if (src_slot >= 0 && src_slot < a.n_tokens && dst_slot >= 0 && dst_slot < a.dst_capacity) {
+                    const char* sp = srow + src_slot * s2 * EB;
+                    u32x4 va = ld16_cached(sp), vb = ld16_cached(sp + ob);
+                    if (rot) rotate_chunks<EB, STYLE>(va, vb, cs, sn);
+                    char* dp = drow + dst_slot * d2 * EB;
+                    st16(dp, va);
+                    st16(dp + ob, vb);
+                } else if (lane == 0 && grp == 0 && a.err_flag) {
+                    atomicOr(a.err_flag, 1);
+                }
+            }
+        }
         return;
     }
 

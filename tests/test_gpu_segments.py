@@ -20,6 +20,8 @@ pytestmark = pytest.mark.gpu
     (2, 4, [48 * 128, 48 * 128 + 1, 5], None),            # 128 runs and one token more: looping blocks
     (2, 4, [48 * 128, 5], None),                          # 128 runs, one per block
     (1, 1, [100, 33], 1 << 20),                           # a loose bound
+    (2, 4, [100, 33, 5000, 49], 20),                      # segments beyond the bound are copied whole
+    (1, 3, [3000, 1, 97], 48),
 ])
 def test_run_edges(L, H, lens, bound):
     d, theta = 128, 5e5
