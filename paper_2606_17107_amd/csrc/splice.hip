@@ -52,6 +52,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kUnroll = 1;         // rows whose loads are issued before any is used
 constexpr int kRowsPerBlock = 1;   // (layer, kv_head) rows per block
 constexpr int kBlock = 256;        // threads per block
+constexpr int64_t kMaxGridX = 0xffffffffll / kBlock;   // blocks: HIP refuses 2^32 threads in one grid dimension
 // Segment mode: a block copies one run of kSegRun consecutive token tiles, whose
 // loads are issued before its first store.  The call is bound by the stream of
 // writes; what matters is how close in memory the writes in flight are and how
@@ -567,9 +568,9 @@ hipError_t launch_splice(const SpliceArgs& a, hipStream_t stream) {
     g.rows_per_block = g.n_rows < kRowsPerBlock ? g.n_rows : kRowsPerBlock;
     int64_t n_tiles = (tokens + g.tok_per_block - 1) / g.tok_per_block;
     const int64_t n_runs = (n_tiles + kSegRun - 1) / kSegRun;
-    g.seg_loop = seg && n_runs > kSegRuns;
-    if (seg) n_tiles = g.seg_loop ? kSegTiles : n_runs;
     const int64_t n_groups = (g.n_rows + g.rows_per_block - 1) / g.rows_per_block;
+    g.seg_loop = seg && (n_runs > kSegRuns || nz * n_runs * n_groups > kMaxGridX);
+    if (seg) n_tiles = !g.seg_loop ? n_runs : n_tiles < kSegTiles ? n_tiles : kSegTiles;
     if (n_tiles > 0x7fffffff || n_groups > 65535 || nz > 65535) return hipErrorInvalidConfiguration;
     // Segment mode sizes the tile axis for the longest segment, so a shorter
     // segment's tiles would all fall on the first XCDs: keep round-robin order.
@@ -579,9 +580,10 @@ hipError_t launch_splice(const SpliceArgs& a, hipStream_t stream) {
     for (int b = 0; b < kPairBits; ++b) g.rho[b] = pow(a.theta, -2.0 * (double)(1 << b) / (double)a.rope_dim);
 
     // Segment mode with row groups divisible by the XCD count: 1-D grid
-    // (decoded in the kernel so that each XCD owns whole row groups).
+    // (decoded in the kernel so that each XCD owns whole row groups), where a grid
+    // dimension holds it.
     const int64_t seg_1d = nz * n_tiles * n_groups;
-    g.seg_xcd = seg && n_groups % kXcds == 0 && seg_1d <= 0x7fffffff;
+    g.seg_xcd = seg && n_groups % kXcds == 0 && seg_1d <= kMaxGridX;
     g.seg_n = (int)nz;
     g.seg_tile_blocks = (int)n_tiles;
     dim3 grid = seg ? (g.seg_xcd ? dim3((unsigned)seg_1d, 1u, 1u)

@@ -48,3 +48,25 @@ def test_run_edges(L, H, lens, bound):
                                      np.arange(sg["dst_pos0"], sg["dst_pos0"] + n, dtype=np.int32), theta, d)
     np.testing.assert_array_equal(host_bits(gv), dst_v)   # every slot no segment owns included
     check_rotated_keys(host_bits(gk), dst_k, 0, d, synth.HALF)
+
+
+@pytest.mark.parametrize("n,L,H,d,bound", [
+    (2979, 8, 8, 256, 88 * 48),     # one token each under a loose bound: in runs, 16.8e6 blocks
+    (65535, 4, 4, 16, 1 << 20),     # the most segments: the looping blocks exceed it as well
+])
+def test_blocks_above_a_launch_dimension(n, L, H, d, bound):
+    """A launch dimension holds 2^32 - 1 threads, 2^24 - 1 blocks of 256."""
+    theta = 1e4
+    log("segments:", n, L, H, bound)
+    g = synth.Draws(11, "cpu")
+    src_k, dst_k = host_bits(g.normal((L, H, n, d))), host_bits(g.normal((L, H, n + 5, d)))
+    src_pos, dst_pos = np.arange(n, dtype=np.int32) % 1000, np.random.default_rng(5).permutation(n).astype(np.int32)
+    segs = [dict(src_slot0=i, dst_seq_base=0, n_tokens=1, src_pos0=int(src_pos[i]), dst_pos0=int(dst_pos[i]),
+                 dst_seq_len=n + 5) for i in range(n)]
+    gk, err = dev(dst_k), torch.zeros(1, dtype=torch.int32, device="cuda")
+    pkv.reposition_splice_batched(dev(src_k), None, gk, None, pkv.make_segments(segs, "cuda"), n, bound, theta, d,
+                                  err_flag=err)
+    torch.cuda.synchronize()
+    assert int(err.item()) == 0
+    oracle.reposition_splice(src_k, None, dst_k, None, src_pos, dst_pos, theta, d)
+    check_rotated_keys(host_bits(gk), dst_k, 0, d, synth.HALF)
