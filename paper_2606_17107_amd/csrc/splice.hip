@@ -53,20 +53,27 @@ constexpr int kUnroll = 1;         // rows whose loads are issued before any is 
 constexpr int kRowsPerBlock = 1;   // (layer, kv_head) rows per block
 constexpr int kBlock = 256;        // threads per block
 constexpr int64_t kMaxGridX = 0xffffffffll / kBlock;   // blocks: HIP refuses 2^32 threads in one grid dimension
-// Segment mode: a block copies one run of kSegRun consecutive token tiles, whose
-// loads are issued before its first store.  The call is bound by the stream of
-// writes; what matters is how close in memory the writes in flight are and how
-// many waves issue them: 16 sequences x 3 skills, 8 layers (4.0 GB), 718 us with
-// 32 blocks a segment and row that loop over tiles 32 apart, six in flight
-// (123 registers); 694 us with the rows dealt to the XCDs in turn; 678 us with
-// runs of three and no loop as well (66 registers; with a loop 727, runs of two /
-// four / five tiles 763 / 704 / 981).  Small compositions lose the blocks that had
-// one tile of six: three heads of 64 in nine sequences 20.5 -> 14.6 us.  Above
-// kSegRuns runs a segment (6144 tokens of 128 + 128 channels) the looping form
-// runs with kSegTiles blocks, so that a loose bound on the segment length does
-// not launch a grid of empty blocks.
+// Segment mode has two forms.  Blocks of the looping form share a segment's tiles
+// in turn (kSegTiles apart, kSegAhead of them in flight), so their number does not
+// grow with the bound on the segment lengths.  Blocks of the run form copy one run
+// of kSegRun consecutive tiles each, without a loop and with half the registers.
+// The call is bound by the stream of writes.  Times of the run form over those of
+// the looping form (1, 8, 15, 64 and 256 rows of one head):
+//   short segments, where a looping block has one or two tiles of its six: 0.36-0.88
+//     up to 1024 tokens (head size 64), 0.36-1.03 (128), 0.31-0.96 up to 512 (256);
+//   longer ones with tiles of 16 tokens (128 + 128 channels bf16, 64 + 64 fp32):
+//     lengths spread over a factor of four 0.78-1.06, all at the bound 0.98-1.08;
+//   longer ones, other tiles: up to 1.55 (head size 64, 16 x 3000 tokens: 239 against
+//     161 us), up to 1.28 (256).
+// An empty block costs 0.6 ns in the run form; the looping form's cost 0.9 ns, 1.7 ns
+// without their early exit.  Above kSegRuns runs a call of mostly short segments
+// under a long bound would lose to 32 looping blocks each (500 x 64 tokens and one
+// of 6000, 125 runs: 2380 us against 970).
 constexpr int kSegRun = 3;
-constexpr int kSegRuns = 128;
+constexpr int kSegRuns = 88;
+constexpr int kSegRunTokens = 16;   // tokens per tile with which long segments take the run form
+constexpr int64_t kSegShort = 1024;
+constexpr int64_t kSegShortTiles = 64;
 constexpr int kSegTiles = 32;      // looping form: token-tile blocks per (row group, segment)
 constexpr int kSegAhead = 6;       // looping form: tiles whose loads are issued before the first store
 constexpr int kHalf = 0;
@@ -569,7 +576,8 @@ hipError_t launch_splice(const SpliceArgs& a, hipStream_t stream) {
     int64_t n_tiles = (tokens + g.tok_per_block - 1) / g.tok_per_block;
     const int64_t n_runs = (n_tiles + kSegRun - 1) / kSegRun;
     const int64_t n_groups = (g.n_rows + g.rows_per_block - 1) / g.rows_per_block;
-    g.seg_loop = seg && (n_runs > kSegRuns || nz * n_runs * n_groups > kMaxGridX);
+    g.seg_loop = seg && (n_runs > kSegRuns || nz * n_runs * n_groups > kMaxGridX ||
+                         (g.tok_per_block != kSegRunTokens && (tokens > kSegShort || n_tiles > kSegShortTiles)));
     if (seg) n_tiles = !g.seg_loop ? n_runs : n_tiles < kSegTiles ? n_tiles : kSegTiles;
     if (n_tiles > 0x7fffffff || n_groups > 65535 || nz > 65535) return hipErrorInvalidConfiguration;
     // Segment mode sizes the tile axis for the longest segment, so a shorter

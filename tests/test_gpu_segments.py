@@ -1,7 +1,9 @@
 """Batched splice at the edges of its partition (a block copies a run of three
-token tiles, 16 tokens each at 8 + 8 lanes a token; above 128 runs 32 blocks
-loop over a segment): segment lengths around one tile, one run and 128 runs, a bound far above the longest segment, row counts
-that do and do not divide over the XCDs, against the fp64 oracle (values
+token tiles, 16 tokens each at 8 + 8 lanes a token; above 88 runs, and for other
+tiles above 1024 tokens or 64 tiles, 32 blocks loop over a segment): segment
+lengths around one tile, one run and the longest of either form, a bound far above
+the longest segment or below it, row counts that do and do not divide over the
+XCDs, more blocks than a launch dimension holds, against the fp64 oracle (values
 bit-exact, keys within one bf16 ulp)."""
 import numpy as np
 import pytest
@@ -17,15 +19,30 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("L,H,lens,bound", [
     (2, 4, [1, 15, 16, 17, 47, 48, 49, 96, 97], None),    # 8 rows: 1-D grid
     (1, 3, [1, 48, 49, 0, 200], None),                    # 3 rows: 3-D grid
-    (2, 4, [48 * 128, 48 * 128 + 1, 5], None),            # 128 runs and one token more: looping blocks
-    (2, 4, [48 * 128, 5], None),                          # 128 runs, one per block
+    (2, 4, [48 * 128, 48 * 128 + 1, 5], None),            # looping blocks, several rounds
+    (2, 4, [48 * 128, 5], None),
+    (2, 4, [48 * 88, 5], None),                           # 88 runs, one per block
+    (2, 4, [48 * 88 + 1, 5], None),                       # one token more: looping blocks
     (1, 1, [100, 33], 1 << 20),                           # a loose bound
     (2, 4, [100, 33, 5000, 49], 20),                      # segments beyond the bound are copied whole
     (1, 3, [3000, 1, 97], 48),
 ])
 def test_run_edges(L, H, lens, bound):
-    d, theta = 128, 5e5
-    log("segments:", L, H, lens, bound)
+    splice_and_check(L, H, 128, lens, bound)
+
+
+@pytest.mark.parametrize("d,lens", [
+    (64, [1024, 5, 33]), (64, [1025, 5, 33]),      # 32 tokens a tile: by the 1024 tokens
+    (256, [512, 5, 9]), (256, [513, 5, 9]),        # 8 tokens a tile: by the 64 tiles
+])
+@pytest.mark.parametrize("L,H", [(2, 4), (1, 3)])
+def test_form_edges(L, H, d, lens):
+    splice_and_check(L, H, d, lens, None)
+
+
+def splice_and_check(L, H, d, lens, bound):
+    theta = 5e5
+    log("segments:", L, H, d, lens, bound)
     g = synth.Draws(7 + len(lens) + H, "cpu")
     S, gap = sum(lens), 7
     src_k, src_v = host_bits(g.normal((L, H, S, d))), host_bits(g.normal((L, H, S, d)))
