@@ -517,7 +517,7 @@ PKV_EXPORT pkv_status pkv_suffix_attention_noalloc(const void* q, const void* k_
                         splits, need, (size_t)PKV_NOALLOC_SCRATCH_BYTES);
         while (splits > 1 && pkv::attention_workspace_bytes(a, splits) > PKV_NOALLOC_SCRATCH_BYTES) --splits;
         need = pkv::attention_workspace_bytes(a, splits);
-        a.auto_splits = 0;   // fewer records than the plan of the library's choice needs
+        // (auto_splits stays: with fewer records the few-row kernels cut the keys into longer runs)
     }
     a.n_splits = splits;
     if (need > 0) {

@@ -99,3 +99,32 @@ def test_explicit_split_count_beyond_the_scratch_is_rejected():
     assert "scratch" in pkv.pkv_last_error()
     torch.cuda.synchronize()
     assert out.untouched(slice(None)), "a rejected call must not write"
+
+
+def test_few_row_plan_lowered_to_fit():
+    """64 sequences of 8 queries, 32 rows a KV head, 8 layers: the planned records (4 a row) exceed the scratch.
+    Fewer records only lengthen the runs of keys, here not at all (four whole sequences and heads a workgroup),
+    so the output equals the workspace call's bit for bit."""
+    L, n, nq, H, Hkv, d, kv = 8, 64, 8, 8, 2, 128, 2048
+    g = synth.Draws(35, "cuda")
+    q, k, v = g.normal((L, n * nq, H, d)), g.normal((L, Hkv, n * kv, d)), g.normal((L, Hkv, n * kv, d))
+    i32 = lambda a: torch.tensor(a, dtype=torch.int32, device="cuda")
+    q_pos, kv_len, cu = i32(list(range(kv - nq, kv)) * n), i32([kv] * n), i32([nq * i for i in range(n + 1)])
+    base = torch.arange(n, dtype=torch.int64, device="cuda") * kv
+    want, out = torch.zeros_like(q), Guarded(q.shape, torch.bfloat16)
+    args = dict(n_seqs=n, cu_q=cu, kv_base=base, max_q=nq)
+    desc = pkv.make_attn_desc(q, k, v, want, kv, **args)
+    need = pkv.pkv_attention_workspace_size(desc, H, Hkv, d)
+    assert need > pkv.PKV_NOALLOC_SCRATCH_BYTES
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    call = (q_pos, kv_len, H, Hkv, d, 1 / math.sqrt(d))
+    assert pkv.pkv_suffix_attention(q, k, v, want, *call, desc, ws, need) == pkv.PKV_OK, pkv.pkv_last_error()
+    desc = pkv.make_attn_desc(q, k, v, out.t, kv, **args)
+    assert pkv.pkv_suffix_attention_noalloc(q, k, v, out.t, *call, desc) == pkv.PKV_OK, pkv.pkv_last_error()
+    torch.cuda.synchronize()
+    out.check("no-alloc output")
+    assert torch.equal(out.t, want)
+    rows = slice((n - 1) * nq, n * nq)
+    want, _ = oracle.attention(host_bits(q[7, rows]), host_bits(k[7, :, -kv:].contiguous()),
+                               host_bits(v[7, :, -kv:].contiguous()), q_pos[rows].cpu().numpy(), kv, 1 / math.sqrt(d))
+    check_attention_close(host_bits(out.t)[7, rows], want)
