@@ -582,6 +582,16 @@ int wgs_per_cu(const AttnArgs& a, const Plan& p) {
     return n < 1 ? 1 : (n > 2 ? 2 : n);               // two waves per SIMD at most (registers)
 }
 
+// Keys one workgroup's rows see at most: with a sliding window, about the window
+// plus the span of the queries (contiguous suffix positions).
+int64_t seen_keys(const AttnArgs& a) {
+    return a.window > 0 && (int64_t)a.window + a.max_q < a.max_kv_len ? (int64_t)a.window + a.max_q : a.max_kv_len;
+}
+
+// Dispatching the longest sequences first costs every workgroup a dependent load
+// and a selection, about 1 us: worth it where a workgroup runs much longer.
+bool order_pays(const AttnArgs& a) { return a.n_seqs > 1 && a.n_seqs <= 64 && seen_keys(a) >= 2048; }
+
 // ---- few query rows (attn_columns.h) -----------------------------------------
 
 // Rows (queries x heads per KV head) of one sequence up to which the few-row
@@ -630,10 +640,7 @@ int attention_splits(const AttnArgs& a) {
     // least 512 keys per split, at most 32 splits.
     const Plan p = make_plan(a, 1);
     const int64_t wgs = (int64_t)p.n_groups * p.rbs;   // workgroups per split
-    // Keys one workgroup's rows see: with a sliding window, about the window
-    // plus the span of the queries (contiguous suffix positions).
-    const int64_t kv = a.window > 0 && (int64_t)a.window + a.max_q < a.max_kv_len ? (int64_t)a.window + a.max_q
-                                                                                  : a.max_kv_len;
+    const int64_t kv = seen_keys(a);
     if (a.dtype == 1) {
         // fp32 path (small problems): one workgroup per CU, at least 64 keys
         // per split, at most 32 splits.
@@ -738,8 +745,7 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t stream) {
     if (n_wg <= 0) return hipSuccess;
     if (n_wg > 0x7fffffff) return hipErrorInvalidValue;
     // More workgroups than the CUs hold at once (bf16 GQA): the order matters.
-    p.longest_first = a.dtype == 0 && a.variant == 0 && a.n_seqs > 1 && a.n_seqs <= 64 &&
-                      n_wg > kCUs * (int64_t)wgs_per_cu(a, p);
+    p.longest_first = a.dtype == 0 && a.variant == 0 && n_wg > kCUs * (int64_t)wgs_per_cu(a, p) && order_pays(a);
     dim3 grid((unsigned)n_wg);
     hipError_t e;
     if (keys) {

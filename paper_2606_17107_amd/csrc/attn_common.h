@@ -63,20 +63,30 @@ __device__ inline bool decode(const Plan& p, int& group, int& rb) {
     return group < p.n_groups && rb < p.rbs;
 }
 
-// The index-th longest sequence (by cache length, ties by number).  Sequences are
-// dispatched longest first when there are more workgroups than slots, so that
-// the last round holds the shortest (16 caches of 8448..12544 keys, 256 queries
-// each, 1024 workgroups for 512 slots: 695 us in the given order, 664 us).
-// n_seqs <= 64: lane s ranks sequence s.
+// The index-th sequence in the order of falling cache lengths (in steps of 1/64 to
+// 1/32 of the bound; ties by number).  Sequences are dispatched longest first when
+// there are more workgroups than slots, so that the last round holds the shortest
+// (16 caches of 8448..12544 keys, 256 queries each, 1024 workgroups for 512 slots:
+// 695 us in the given order, 664 us).  n_seqs <= 64: lane s holds sequence s, and
+// six ballots select, bit by bit of the length, the group that `index` falls in.
+// (Ranking every sequence against every other took 3 us: 8 layers of 64 sequences
+// of 64 keys 52 -> 80 us.)
 __device__ inline int longest_seq(const AttnArgs& a, int index) {
     const int s = (int)__lane_id();
-    const int len = s < a.n_seqs ? a.kv_len[s] : -1;
-    int rank = 0;
-    for (int t = 0; t < a.n_seqs; ++t) {
-        const int other = __builtin_amdgcn_readlane(len, t);
-        rank += other > len || (other == len && t < s);
+    const int len = s < a.n_seqs ? min(max(a.kv_len[s], 0), a.max_kv_len) : 0;
+    const int key = len >> max(0, 26 - __builtin_clz(a.max_kv_len | 1));   // below 64
+    uint64_t group = a.n_seqs >= 64 ? ~0ull : (1ull << a.n_seqs) - 1;
+    int k = index;
+#pragma unroll
+    for (int bit = 5; bit >= 0; --bit) {
+        const uint64_t longer = group & __builtin_amdgcn_ballot_w64((key >> bit) & 1);
+        const int n = __builtin_popcountll(longer);
+        group = k < n ? longer : group & ~longer;
+        k = k < n ? k : k - n;
     }
-    const uint64_t at = __builtin_amdgcn_ballot_w64(s < a.n_seqs && rank == index);
+    // The k-th lane of the group.
+    const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(group >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)group, 0));
+    const uint64_t at = group & __builtin_amdgcn_ballot_w64(before == k);
     return at ? __builtin_ctzll(at) : index;
 }
 

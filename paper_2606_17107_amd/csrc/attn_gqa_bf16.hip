@@ -33,7 +33,9 @@ constexpr int kWaves = 4;
 constexpr int kStages = 4;
 constexpr int kAhead = 3;    // LDS operand reads issued this many operands ahead of their MFMA
 
-template <int D, bool PAGED>
+// ORDERED: sequences are dispatched longest first (an instantiation of its own: the
+// selection costs a one-round call 0.3 us by being there).
+template <int D, bool PAGED, bool ORDERED>
 __global__ __launch_bounds__(kWaves * 64, 2) void attn_gqa_bf16_kernel(AttnArgs a, Plan p) {
     constexpr int QB = kQB, NW = kWaves, NS = kStages;
     constexpr int CH = D / 8;              // 16-byte chunks per row
@@ -64,7 +66,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_gqa_bf16_kernel(AttnArgs 
     rest /= a.n_kv_heads;
     const int layer = rest % a.n_layers;
     int seq = rest / a.n_layers;
-    if (p.longest_first) seq = longest_seq(a, seq);
+    if constexpr (ORDERED) seq = longest_seq(a, seq);
     const SeqInfo si = seq_info(a, seq);
     const int M = si.nq * p.G;
     const int m0 = rb * (NW * 32 * QB);
@@ -691,7 +693,10 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_gqa_bf16_kernel(AttnArgs 
 template <int D, bool PAGED>
 hipError_t launch_d(const AttnArgs& a, const Plan& p, dim3 grid, hipStream_t stream) {
     if (p.nw != kWaves || p.qb != kQB || p.ns != kStages) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((attn_gqa_bf16_kernel<D, PAGED>), grid, dim3(kWaves * 64), 0, stream, a, p);
+    if (p.longest_first)
+        hipLaunchKernelGGL((attn_gqa_bf16_kernel<D, PAGED, true>), grid, dim3(kWaves * 64), 0, stream, a, p);
+    else
+        hipLaunchKernelGGL((attn_gqa_bf16_kernel<D, PAGED, false>), grid, dim3(kWaves * 64), 0, stream, a, p);
     return hipGetLastError();
 }
 

@@ -43,6 +43,48 @@ def test_longest_first(n, nq, L, d):
         check_attention_close(got[l], np.concatenate(want))
 
 
+@pytest.mark.parametrize("n,nq,L,d", [(2, 40, 48, 64), (7, 33, 12, 128), (64, 9, 3, 64)])
+def test_longest_first_long_caches(n, nq, L, d):
+    """Caches long enough for the order to pay (2048 keys and more), in no order: equal lengths, lengths above the
+    stated bound (cut to it) and a negative one, contiguous and paged, against the oracle on the first and last
+    layer.  The order is by 1/64 of the bound, so equal classes occur as well."""
+    H, Hkv, bound, page = 16, 4, 2100, 64
+    kv = [min(bound + 5, 30 + (i * 977) % 2200) for i in range(n)]
+    kv[n // 2] = kv[0]
+    kv[1] = -3 if n > 2 else kv[1]
+    own = [min(max(m, 0), bound) for m in kv]
+    log("longest first, long caches: %d sequences, %d layers, d %d" % (n, L, d))
+    g = synth.Draws(190 + n, "cuda")
+    base = np.concatenate([[0], np.cumsum([-(-m // page) * page + page for m in own])]).astype(np.int64)
+    q, k, v = g.normal((L, n * nq, H, d)), g.normal((L, Hkv, int(base[-1]), d)), g.normal((L, Hkv, int(base[-1]), d))
+    q_pos = np.concatenate([np.arange(max(m, nq) - nq, max(m, nq)) for m in own]).astype(np.int32)
+    i32 = lambda a: torch.tensor(a, dtype=torch.int32, device="cuda")
+    args = dict(n_seqs=n, cu_q=i32([nq * i for i in range(n + 1)]), max_q=nq, n_splits=1)
+    out, out_p = Guarded((L, n * nq, H, d), torch.bfloat16), Guarded((L, n * nq, H, d), torch.bfloat16)
+    pkv.suffix_attention(q, k, v, out.t, i32(q_pos.tolist()), i32(kv), 1 / math.sqrt(d), bound,
+                         kv_base=torch.from_numpy(base[:n]).cuda(), **args)
+    # the same cache as pages: [layer][page][slot][head][channel]
+    pool = lambda t: t.view(L, Hkv, -1, page, d).permute(0, 2, 3, 1, 4).contiguous()
+    per = -(-bound // page)
+    table = i32([[min(base[s] // page + e, base[-1] // page - 1) for e in range(per)] for s in range(n)])
+    pkv.suffix_attention_paged(q, pool(k), pool(v), out_p.t, i32(q_pos.tolist()), i32(kv), table, 1 / math.sqrt(d), bound,
+                               **args)
+    torch.cuda.synchronize()
+    out.check("attention output")
+    out_p.check("paged attention output")
+    assert torch.equal(out.t, out_p.t)
+    got, qh, kh, vh = host_bits(out.t), host_bits(q), host_bits(k), host_bits(v)
+    for l in (0, L - 1):
+        want = []
+        for s in range(n):
+            r, c = slice(s * nq, (s + 1) * nq), slice(base[s], base[s] + own[s])
+            want.append(oracle.attention(np.ascontiguousarray(qh[l, r]), np.ascontiguousarray(kh[l][:, c]),
+                                         np.ascontiguousarray(vh[l][:, c]), q_pos[r], own[s], 1 / math.sqrt(d))[0]
+                        if own[s] else np.zeros((nq, H, d)))
+        # one bf16 ulp of outputs of size 4 (few visible keys) is 2^-6
+        check_attention_close(got[l], np.concatenate(want), max_abs=2e-2 if np.abs(want).max() < 2.5 else 2 ** -5)
+
+
 @pytest.mark.parametrize("variant,H,Hkv,d,nq,splits", [
     ("gqa", 8, 1, 64, 150, 1),      # 1 group, 10 row blocks: shared by 8 XCDs
     ("gqa", 8, 2, 128, 97, 3),      # 6 groups, 4 row blocks
