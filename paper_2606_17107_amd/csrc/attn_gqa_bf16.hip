@@ -92,7 +92,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_gqa_bf16_kernel(AttnArgs 
     }
     // Positions, then the Q^T B operands (8 channels of the row per k-step): the
     // key-range set-up needs the positions only, so the Q loads stay in flight
-    // over it.  Rows past M repeat row 0 (never written).
+    // over it.  Rows past M load nothing (one query of one head in 128 rows, 512
+    // sequences x heads: 478 us when they repeat row 0, 446 us).
     int pos[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) pos[qb] = a.q_pos[si.q0 + qi[qb]];
@@ -101,8 +102,15 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_gqa_bf16_kernel(AttnArgs 
     for (int qb = 0; qb < QB; ++qb) {
         const uint16_t* qrow = (const uint16_t*)a.q + (int64_t)layer * a.q_stride[0] +
                                (int64_t)(si.q0 + qi[qb]) * a.q_stride[1] + (int64_t)head[qb] * a.q_stride[2];
+        u32x4 v[KS];
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qrow + ks * 16 + hl * 8));
+        for (int ks = 0; ks < KS; ++ks) v[ks] = u32x4{0u, 0u, 0u, 0u};
+        if (row_ok[qb]) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) v[ks] = *(const u32x4*)(qrow + ks * 16 + hl * 8);
+        }
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = __builtin_bit_cast(bf16x8, v[ks]);
     }
 
     int rmax = 0, rmin = 0x7fffffff, smin = 0x7fffffff, smax = 0;
