@@ -604,10 +604,40 @@ constexpr int kRowsMla = 16;
 
 int64_t col_items(const AttnArgs& a) { return (int64_t)a.n_layers * a.n_kv_heads * a.n_seqs; }
 
+// Whole items, one workgroup each: many items (the last round is a small part of
+// the call), or short ones, where one launch without a merge is faster (4 sequences;
+// whole / cut / many-row kernel: GQA, 8 KV heads of 128, 768 keys 13.1 / 13.3 / 21.5
+// us, 1024 keys 15.7 / 13.3 / 18.9; of 64, 768 keys 10.2 / 12.0 / 17.7, 1024 keys
+// 11.7 / 12.1 / 16.4; MLA, 16 heads, 512 keys 21.8 / 23.6 / 33.8, 768 keys 27.3 /
+// 24.4 / 46.0).  Head size 64 has two workgroups a CU, but columns use one: whole
+// items up to twice the length when they outnumber the slots.
+bool col_whole(const AttnArgs& a) {
+    const int64_t items = col_items(a);
+    const int64_t cut = a.variant == 1 ? 512 : a.head_dim == 128 ? 832 : items > 2 * kCUs ? 2048 : 1024;
+    return items >= 8 * kCUs || seen_keys(a) < cut;
+}
+
+// Starting an item costs the few-row kernels more than the many-row ones, the more
+// so the more rows it merges, and outside head size 64 their tiles leave one
+// workgroup a CU, where the many-row GQA kernel has two.  So short caches stay with
+// the many-row kernels: two tiles of keys for more than 8 rows (64 keys, 32 rows, 8
+// KV heads of 128: 7.7 us against 8.7; 4 rows: 7.1 against 7.0), and, with more items
+// than CUs (head size 64: than two a CU), until the stream of keys outweighs the
+// rounds (64 sequences, 8 KV heads of 128: all of 512 keys 28.9 us against 31.3, all
+// of 1024 keys 49.5 against 50.4, up to 1024 keys 39.5 against 35.9).
+bool col_long_enough(const AttnArgs& a, int64_t rows) {
+    const int64_t kv = seen_keys(a), items = col_items(a);
+    if (a.head_dim != 64 && rows > 8 && kv <= 2 * kColTile) return false;
+    if (a.variant == 1 || items <= kCUs) return true;
+    if (a.head_dim == 64) return items <= 2 * kCUs || kv >= 512;
+    return kv >= (items >= 8 * kCUs ? 2048 : 1024);
+}
+
 bool col_route(const AttnArgs& a) {
     if (!a.auto_splits || a.dtype != 0 || a.n_seqs > kColMaxSeqs) return false;
     const int64_t rows = (int64_t)a.max_q * (a.n_heads / a.n_kv_heads);
-    if (rows < 1 || rows > (a.variant == 1 ? kRowsMla : kRowsGqa)) return false;
+    if (rows < 1 || rows > (a.variant == 1 ? kRowsMla : kRowsGqa) || !col_long_enough(a, rows))
+        return false;
     // axis positions and workgroup ids are 32-bit
     return col_items(a) * ((int64_t)a.max_kv_len / kColTile + 16) < 0x7fffffff;
 }
@@ -615,13 +645,11 @@ bool col_route(const AttnArgs& a) {
 }  // namespace
 
 int attention_splits(const AttnArgs& a) {
-    if (a.n_splits == 0 && a.n_seqs > 1 && col_route(a)) {
-        // Many items: whole ones (the last round is a small part of the call).
-        // Otherwise columns, with records for twice the pieces that sequences
-        // of one length would be cut into (a sequence longer than that makes
-        // the columns longer).
+    if (a.n_splits == 0 && col_route(a)) {
+        // Columns have records for twice the pieces that sequences of one length
+        // would be cut into (a sequence longer than that makes the columns longer).
+        if (col_whole(a)) return 1;
         const int64_t items = col_items(a);
-        if (items >= 8 * kCUs) return 1;
         return (int)std::min<int64_t>(32, 2 * ((kCUs + items - 1) / items) + 2);
     }
     if (a.n_splits > 0) {

@@ -95,8 +95,8 @@ __global__ __launch_bounds__(kMlaRowWaves * 64, 1) void attn_mla_rows_kernel(Att
             x += sg.length;
             if (sg.first == sg.last) continue;   // uniform
         } else {
-            sg.stream = (int)(column / (uint32_t)a.n_seqs);
-            sg.seq = (int)(column - (uint32_t)sg.stream * (uint32_t)a.n_seqs);
+            sg.seq = (int)(column / (uint32_t)p.streams);   // by sequence: neighbours take about equally long
+            sg.stream = (int)(column - (uint32_t)sg.seq * (uint32_t)p.streams);
             sg.first = 0;
             sg.last = sg.tiles = 1;
             sg.piece = 0;

@@ -336,6 +336,39 @@ def test_split_planner_sizes_windowed_work_by_the_window():
     assert planned_splits(1, 32, 8, 128, 128, 64, 8256, window=10000) == 16   # window past the cache
 
 
+def few_row_records(L, H, Hkv, d, n, q, kv, window=0):
+    """Records a row that the library plans for n sequences of q queries (1: none), through the workspace size."""
+    mla, dv = d == 576, 512 if d == 576 else d
+    d_ = attn_desc(variant=int(mla), n_layers=L, n_seqs=n, head_dim_v=dv, total_q=n * q, max_q=q, max_kv_len=kv,
+                   cache_slots=n * kv, window=window, cu_q=BASE)
+    d_.q_stride = pkv._i64x3(n * q * H * d, H * d, d)
+    d_.k_stride = d_.v_stride = pkv._i64x3(Hkv * n * kv * d, n * kv * d, d)
+    d_.o_stride = pkv._i64x3(n * q * H * dv, H * dv, dv)
+    need, record = pkv.pkv_attention_workspace_size(d_, H, Hkv, d), L * n * q * H * (dv + 1) * 4
+    assert need % record == 0
+    return max(1, need // record)
+
+
+def test_split_planner_few_rows():
+    """Few query rows: short caches take one launch, without records (a workgroup per sequence and KV head, or
+    the many-row kernels); longer ones are cut into columns, with records for twice the pieces that
+    sequences of one length need plus two, at most 32.  One sequence is planned like several."""
+    for n in (1, 4):
+        assert few_row_records(1, 32, 8, 128, n, 1, 831) == 1
+        assert few_row_records(1, 32, 8, 128, n, 1, 832) == {1: 32, 4: 18}[n]
+        assert few_row_records(1, 32, 8, 64, n, 8, 1023) == 1
+        assert few_row_records(1, 32, 8, 64, n, 8, 1024) == {1: 32, 4: 18}[n]
+        assert few_row_records(1, 16, 1, 576, n, 1, 511) == 1
+        assert few_row_records(1, 16, 1, 576, n, 1, 512) == 32
+    assert few_row_records(1, 32, 8, 128, 4, 1, 50000, window=500) == 1      # the window bounds the keys
+    assert few_row_records(1, 32, 8, 128, 4, 1, 50000, window=900) == 18
+    assert few_row_records(1, 32, 8, 128, 64, 1, 1023) == 1                  # 512 items: many-row kernels below
+    assert few_row_records(1, 32, 8, 128, 64, 1, 1024) == 4
+    assert few_row_records(8, 32, 32, 64, 3, 1, 2047) == 1                   # 768 items of head size 64
+    assert few_row_records(8, 32, 32, 64, 3, 1, 2048) == 4
+    assert few_row_records(8, 32, 32, 64, 64, 1, 50000) == 1                 # 2048 items and more: never cut
+
+
 def test_split_planner_fp32():
     """fp32: split until there is about one workgroup per CU, at least 64 keys per split, at most 32."""
     assert planned_splits(1, 4, 2, 64, 64, 16, 528, dtype=1) == 8       # tiny: 2 workgroups, 528 keys

@@ -35,6 +35,25 @@ CASES = {
     "MLA, 8 heads, two queries": dict(H=8, Hkv=1, d=576, nq=[2, 1, 0, 2], kv=[300, 40, 9, 1111]),
     "MLA, paged, window": dict(H=16, Hkv=1, d=576, nq=[1, 1], kv=[600, 2100], page=64, window=333),
     "MLA, 24 rows (many-row kernel)": dict(H=8, Hkv=1, d=576, nq=[3], kv=[500]),
+    # lengths around which a call changes its kernel or its partition
+    "64 keys, 8 rows": dict(H=8, Hkv=1, d=128, nq=[1, 1], kv=[64, 7]),
+    "64 keys, 9 rows (many-row kernel)": dict(H=9, Hkv=1, d=128, nq=[1, 1], kv=[64, 7]),
+    "65 keys, 9 rows": dict(H=9, Hkv=1, d=128, nq=[1, 1], kv=[65, 7]),
+    "831 keys, whole": dict(H=8, Hkv=2, d=128, nq=[1, 2, 1], kv=[831, 40, 500]),
+    "832 keys, cut": dict(H=8, Hkv=2, d=128, nq=[1, 2, 1], kv=[832, 40, 500]),
+    "1023 keys of 64 channels, whole": dict(H=8, Hkv=2, d=64, nq=[1, 2, 1], kv=[1023, 40, 500]),
+    "1024 keys of 64 channels, cut": dict(H=8, Hkv=2, d=64, nq=[1, 2, 1], kv=[1024, 40, 500]),
+    "one sequence cut into 32": dict(H=4, Hkv=1, d=128, nq=[1], kv=[8200]),
+    "320 items, 1023 keys (many-row kernel)": dict(H=8, Hkv=8, d=128, nq=[1] * 40, kv=[5] * 20 + [1023] + [9] * 19),
+    "320 items, 1024 keys": dict(H=8, Hkv=8, d=128, nq=[1] * 40, kv=[5] * 20 + [1024] + [9] * 19),
+    "640 items of 64 channels, 511 keys (many-row kernel)": dict(H=16, Hkv=16, d=64, nq=[1] * 40,
+                                                                 kv=[5] * 20 + [511] + [9] * 19),
+    "640 items of 64 channels, 512 keys, whole": dict(H=16, Hkv=16, d=64, nq=[1] * 40, kv=[5] * 20 + [512] + [9] * 19),
+    "640 items of 64 channels, 2048 keys, cut": dict(H=16, Hkv=16, d=64, nq=[1] * 40, kv=[5] * 20 + [2048] + [9] * 19),
+    "2048 items, 2047 keys (many-row kernel)": dict(H=32, Hkv=32, d=128, nq=[1] * 64, kv=[5] * 20 + [2047] + [3] * 43),
+    "2048 items, 2048 keys, whole": dict(H=32, Hkv=32, d=128, nq=[1] * 64, kv=[5] * 20 + [2048] + [3] * 43),
+    "MLA, 511 keys, whole": dict(H=16, Hkv=1, d=576, nq=[1, 1], kv=[511, 40]),
+    "MLA, 512 keys, cut": dict(H=16, Hkv=1, d=576, nq=[1, 1], kv=[512, 40]),
 }
 
 
