@@ -154,13 +154,19 @@ def _keep_until_done(t: Optional[torch.Tensor], stream) -> None:
         t.record_stream(stream)
 
 
+# torch's raw accessors of the current stream and device; private, so a torch
+# without them is served by the public ones.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
         # torch's current stream on the current device, by the raw accessors once
         # torch has initialised the GPU: current_stream() looks the device up
         # through the environment and builds a Stream object (4 us a call).
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _raw_stream is not None and _raw_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_raw_device())
         return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
     if isinstance(stream, int):
         return stream

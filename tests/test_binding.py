@@ -39,3 +39,21 @@ def test_need_checks_type_dtype_size_and_device():
         pkv._need(pos, "kv_len", meta, torch.int32, 1)
     with pytest.raises(TypeError, match="must be a torch.Tensor"):
         pkv._need([0] * 10, "dst_pos", cpu, torch.int32, 10)
+
+
+def test_stream_lookup_without_the_raw_accessors(monkeypatch):
+    """The private accessors are optional: without either of them the public call serves."""
+    class Current:
+        cuda_stream = 77
+
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "is_available", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Current)
+    monkeypatch.setattr(pkv, "_raw_device", lambda: 3)
+    monkeypatch.setattr(pkv, "_raw_stream", lambda device: 100 + device)
+    assert pkv._stream(None) == 103
+    monkeypatch.setattr(pkv, "_raw_stream", None)
+    assert pkv._stream(None) == 77
+    monkeypatch.setattr(pkv, "_raw_stream", lambda device: 100 + device)
+    monkeypatch.setattr(pkv, "_raw_device", None)
+    assert pkv._stream(None) == 77
