@@ -33,9 +33,12 @@ constexpr int kWaves = 4;
 constexpr int kStages = 4;
 constexpr int kAhead = 3;    // LDS operand reads issued this many operands ahead of their MFMA
 
-// ORDERED: sequences are dispatched longest first (an instantiation of its own: the
-// selection costs a one-round call 0.3 us by being there).
-template <int D, bool PAGED, bool ORDERED>
+// FORM: what differs between calls at the start of a workgroup (instantiations of
+// their own, since an option costs a one-round call up to 0.5 us by being there).
+// kFull: every row block but the last of a sequence is full.  kFew: no sequence
+// fills its one row block.  kOrdered: sequences are dispatched longest first.
+enum { kFull, kFew, kOrdered };
+template <int D, bool PAGED, int FORM>
 __global__ __launch_bounds__(kWaves * 64, 2) void attn_gqa_bf16_kernel(AttnArgs a, Plan p) {
     constexpr int QB = kQB, NW = kWaves, NS = kStages;
     constexpr int CH = D / 8;              // 16-byte chunks per row
@@ -66,7 +69,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_gqa_bf16_kernel(AttnArgs 
     rest /= a.n_kv_heads;
     const int layer = rest % a.n_layers;
     int seq = rest / a.n_layers;
-    if constexpr (ORDERED) seq = longest_seq(a, seq);
+    if constexpr (FORM == kOrdered) seq = longest_seq(a, seq);
     const SeqInfo si = seq_info(a, seq);
     const int M = si.nq * p.G;
     const int m0 = rb * (NW * 32 * QB);
@@ -92,8 +95,10 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_gqa_bf16_kernel(AttnArgs 
     }
     // Positions, then the Q^T B operands (8 channels of the row per k-step): the
     // key-range set-up needs the positions only, so the Q loads stay in flight
-    // over it.  Rows past M load nothing (one query of one head in 128 rows, 512
-    // sequences x heads: 478 us when they repeat row 0, 446 us).
+    // over it.  Rows past M repeat row 0 (never written) in full workgroups, where a
+    // branch costs more (64 queries x 4 heads over 8256 keys: 29.9 us against 29.5),
+    // and load nothing in others (8 layers of 64 sequences, one query of 4 heads over
+    // 512 keys: 229 us when they repeat row 0, 214 us).
     int pos[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) pos[qb] = a.q_pos[si.q0 + qi[qb]];
@@ -105,7 +110,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_gqa_bf16_kernel(AttnArgs 
         u32x4 v[KS];
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) v[ks] = u32x4{0u, 0u, 0u, 0u};
-        if (row_ok[qb]) {
+        if (FORM == kFull || row_ok[qb]) {
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) v[ks] = *(const u32x4*)(qrow + ks * 16 + hl * 8);
         }
@@ -701,10 +706,13 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_gqa_bf16_kernel(AttnArgs 
 template <int D, bool PAGED>
 hipError_t launch_d(const AttnArgs& a, const Plan& p, dim3 grid, hipStream_t stream) {
     if (p.nw != kWaves || p.qb != kQB || p.ns != kStages) return hipErrorInvalidValue;
+    const dim3 block(kWaves * 64);
     if (p.longest_first)
-        hipLaunchKernelGGL((attn_gqa_bf16_kernel<D, PAGED, true>), grid, dim3(kWaves * 64), 0, stream, a, p);
+        hipLaunchKernelGGL((attn_gqa_bf16_kernel<D, PAGED, kOrdered>), grid, block, 0, stream, a, p);
+    else if ((int64_t)a.max_q * p.G < p.BM)
+        hipLaunchKernelGGL((attn_gqa_bf16_kernel<D, PAGED, kFew>), grid, block, 0, stream, a, p);
     else
-        hipLaunchKernelGGL((attn_gqa_bf16_kernel<D, PAGED, false>), grid, dim3(kWaves * 64), 0, stream, a, p);
+        hipLaunchKernelGGL((attn_gqa_bf16_kernel<D, PAGED, kFull>), grid, block, 0, stream, a, p);
     return hipGetLastError();
 }
 
