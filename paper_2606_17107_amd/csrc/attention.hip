@@ -609,11 +609,15 @@ int64_t col_items(const AttnArgs& a) { return (int64_t)a.n_layers * a.n_kv_heads
 // whole / cut / many-row kernel: GQA, 8 KV heads of 128, 768 keys 13.1 / 13.3 / 21.5
 // us, 1024 keys 15.7 / 13.3 / 18.9; of 64, 768 keys 10.2 / 12.0 / 17.7, 1024 keys
 // 11.7 / 12.1 / 16.4; MLA, 16 heads, 512 keys 21.8 / 23.6 / 33.8, 768 keys 27.3 /
-// 24.4 / 46.0).  Head size 64 has two workgroups a CU, but columns use one: whole
+// 24.4 / 46.0; 64 MLA sequences of which one has 512 keys, the others 32: 21.6 / 18.8,
+// so several are cut a little earlier than one).  Head size 64 has two workgroups a CU, but columns use one: whole
 // items up to twice the length when they outnumber the slots.
 bool col_whole(const AttnArgs& a) {
     const int64_t items = col_items(a);
-    const int64_t cut = a.variant == 1 ? 512 : a.head_dim == 128 ? 832 : items > 2 * kCUs ? 2048 : 1024;
+    const int64_t cut = a.variant == 1       ? (a.n_seqs == 1 ? 640 : 512)
+                        : a.head_dim == 128  ? 832
+                        : items > 2 * kCUs   ? 2048
+                                             : 1024;
     return items >= 8 * kCUs || seen_keys(a) < cut;
 }
 

@@ -358,8 +358,8 @@ def test_split_planner_few_rows():
         assert few_row_records(1, 32, 8, 128, n, 1, 832) == {1: 32, 4: 18}[n]
         assert few_row_records(1, 32, 8, 64, n, 8, 1023) == 1
         assert few_row_records(1, 32, 8, 64, n, 8, 1024) == {1: 32, 4: 18}[n]
-        assert few_row_records(1, 16, 1, 576, n, 1, 511) == 1
-        assert few_row_records(1, 16, 1, 576, n, 1, 512) == 32
+        assert few_row_records(1, 16, 1, 576, n, 1, {1: 639, 4: 511}[n]) == 1
+        assert few_row_records(1, 16, 1, 576, n, 1, {1: 640, 4: 512}[n]) == 32
     assert few_row_records(1, 32, 8, 128, 4, 1, 50000, window=500) == 1      # the window bounds the keys
     assert few_row_records(1, 32, 8, 128, 4, 1, 50000, window=900) == 18
     assert few_row_records(1, 32, 8, 128, 64, 1, 1023) == 1                  # 512 items: many-row kernels below

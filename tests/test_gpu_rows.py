@@ -56,6 +56,8 @@ CASES = {
     "2048 items, 2047 keys (many-row kernel)": dict(H=32, Hkv=32, d=128, nq=[1] * 64, kv=[5] * 20 + [2047] + [3] * 43),
     "2048 items, 2048 keys, whole": dict(H=32, Hkv=32, d=128, nq=[1] * 64, kv=[5] * 20 + [2048] + [3] * 43),
     "MLA, 511 keys, whole": dict(H=16, Hkv=1, d=576, nq=[1, 1], kv=[511, 40]),
+    "MLA, one sequence of 639 keys, whole": dict(H=16, Hkv=1, d=576, nq=[1], kv=[639]),
+    "MLA, one sequence of 640 keys, cut": dict(H=16, Hkv=1, d=576, nq=[1], kv=[640]),
     "MLA, 512 keys, cut": dict(H=16, Hkv=1, d=576, nq=[1, 1], kv=[512, 40]),
     "scale 0": dict(H=8, Hkv=2, d=128, nq=[3, 1, 2], kv=[800, 33, 2000], window=100, scale=0.0),
     "negative scale": dict(H=8, Hkv=2, d=64, nq=[3, 1, 2], kv=[800, 33, 2000], scale=-0.1),
