@@ -576,14 +576,16 @@ def source_hash(files):
     return h.hexdigest()[:16]
 
 
-KERNEL_SOURCES = {   # the kernel's translation unit first, then the headers it includes
+KERNEL_SOURCES = {   # the kernel's translation unit first, then the headers it includes and its dispatch
     "splice_kernel": ["paper_2606_17107_amd/csrc/splice.hip", "paper_2606_17107_amd/csrc/pkv_internal.h"],
-    "attn_gqa_bf16": ["paper_2606_17107_amd/csrc/attn_gqa_bf16.hip", "paper_2606_17107_amd/csrc/attn_common.h",
-                      "paper_2606_17107_amd/csrc/attention.hip", "paper_2606_17107_amd/csrc/pkv_internal.h"],
-    "attn_mla_bf16": ["paper_2606_17107_amd/csrc/attn_mla_bf16.hip", "paper_2606_17107_amd/csrc/attn_common.h",
-                      "paper_2606_17107_amd/csrc/attention.hip", "paper_2606_17107_amd/csrc/pkv_internal.h"],
+    "attn_gqa_bf16": ["paper_2606_17107_amd/csrc/attn_gqa_bf16.hip", "paper_2606_17107_amd/csrc/attn_gqa_tile.h",
+                      "paper_2606_17107_amd/csrc/attn_common.h", "paper_2606_17107_amd/csrc/attention.hip",
+                      "paper_2606_17107_amd/csrc/attn_columns.h", "paper_2606_17107_amd/csrc/pkv_internal.h"],
+    "attn_mla_bf16": ["paper_2606_17107_amd/csrc/attn_mla_bf16.hip", "paper_2606_17107_amd/csrc/attn_mla_tile.h",
+                      "paper_2606_17107_amd/csrc/attn_common.h", "paper_2606_17107_amd/csrc/attention.hip",
+                      "paper_2606_17107_amd/csrc/attn_columns.h", "paper_2606_17107_amd/csrc/pkv_internal.h"],
     "attn_gqa_f32": ["paper_2606_17107_amd/csrc/attention.hip", "paper_2606_17107_amd/csrc/attn_common.h",
-                     "paper_2606_17107_amd/csrc/pkv_internal.h"],
+                     "paper_2606_17107_amd/csrc/attn_columns.h", "paper_2606_17107_amd/csrc/pkv_internal.h"],
 }
 
 

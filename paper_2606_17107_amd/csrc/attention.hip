@@ -610,8 +610,9 @@ int64_t col_items(const AttnArgs& a) { return (int64_t)a.n_layers * a.n_kv_heads
 // us, 1024 keys 15.7 / 13.3 / 18.9; of 64, 768 keys 10.2 / 12.0 / 17.7, 1024 keys
 // 11.7 / 12.1 / 16.4; MLA, 16 heads, 512 keys 21.8 / 23.6 / 33.8, 768 keys 27.3 /
 // 24.4 / 46.0; 64 MLA sequences of which one has 512 keys, the others 32: 21.6 / 18.8,
-// so several are cut a little earlier than one).  Head size 64 has two workgroups a CU, but columns use one: whole
-// items up to twice the length when they outnumber the slots.
+// so several are cut a little earlier than one).  Head size 64 has two workgroups a
+// CU, but columns use one: whole items up to twice the length when they outnumber
+// the slots.
 bool col_whole(const AttnArgs& a) {
     const int64_t items = col_items(a);
     const int64_t cut = a.variant == 1       ? (a.n_seqs == 1 ? 640 : 512)
@@ -750,9 +751,12 @@ hipError_t launch_columns(const AttnArgs& a, hipStream_t stream) {
     p.G = a.n_heads / a.n_kv_heads;
     p.streams = a.n_layers * a.n_kv_heads;
     p.pieces = a.n_splits;
-    p.columns = p.pieces > 1 ? kCUs : 0;   // one workgroup per CU (its tiles fill the LDS)
+    // One workgroup per CU: its tiles fill the LDS, except at head size 64, where a
+    // second one would fit.
+    p.columns = p.pieces > 1 ? kCUs : 0;
     // Measured costs of a column's shortest useful run and of starting an item
-    // (set-up, first loads and merge: about 7 us), in tiles of one workgroup.
+    // (set-up, first loads and merge: about 7 us), in tiles of one workgroup at head
+    // size 128; the tiles of head size 64 take half as long, with the same counts.
     p.min_tiles = a.variant == 1 ? 4 : 8;
     p.item_cost = a.variant == 1 ? 4 : 12;
     const int64_t cols = p.columns ? p.columns : (col_items(a) + kXcds - 1) / kXcds * kXcds;

@@ -4,10 +4,13 @@
 // The key tiles of every (layer, KV head) stream and sequence are laid end to
 // end on one axis (stream-major, then sequence), and the axis is cut into
 // columns of equal length, one workgroup each, so all workgroups get the same
-// number of tiles however ragged the cache lengths are.  A column's run of tiles covers the end of one item
-// (stream, sequence), any number of whole items, and the beginning of another:
-// an item inside one column is finished there, an item cut by column borders
-// leaves one partial per column for the combine pass.
+// number of tiles however ragged the cache lengths are.  A column's run of tiles
+// covers the end of one item (stream, sequence), any number of whole items, and
+// the beginning of another: an item inside one column is finished there, an item
+// cut by column borders leaves one partial per column for the combine pass.  The
+// borders follow all lengths of the call, so where one sequence is cut, and with
+// it the rounding of its result, depends on the others.  Short caches are not cut:
+// a workgroup takes a whole item, and sequences do not affect each other.
 #pragma once
 
 #include "attn_common.h"
@@ -19,9 +22,9 @@ constexpr int kColMaxSeqs = 64;   // one lane of a wave per sequence
 
 // Wave reductions and prefix sum by DPP (a register move within the wave: no
 // trip through LDS, whose six dependent round trips cost about 0.4 us a
-// reduction).  Rotations within the 16-lane
-// rows leave every row's result in all its lanes; the four rows are combined in
-// scalar registers, so the result is uniform.
+// reduction).  Rotations within the 16-lane rows leave every row's result in all
+// its lanes; the four rows are combined in scalar registers, so the result is
+// uniform.
 template <int CTRL, int ROWS = 0xf>
 __device__ inline int dpp(int old, int v) {
     return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWS, 0xf, false);

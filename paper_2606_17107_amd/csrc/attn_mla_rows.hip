@@ -2,8 +2,9 @@
 // generation with up to 16 (query, head) rows a sequence (paper Sec. 8, MLA
 // adapter; Sec. 5 "Linear-time TTFT").
 //
-// 16 rows are all heads of one query of a 16-head model.  The call is bound by the stream of latent rows from HBM, so, as in the GQA few-row
-// kernel, the workgroup splits the KEYS over its waves:
+// 16 rows are all heads of one query of a 16-head model.  The call is bound by the
+// stream of latent rows from HBM, so, as in the GQA few-row kernel, the workgroup
+// splits the KEYS over its waves:
 //   * MFMA 16x16x32 bf16 (N = 16 rows, no idle columns).  Every wave holds the
 //     16 rows' Q^T over 576 channels (72 VGPRs) and their O^T over 512 channels
 //     (128 VGPRs) and takes every fourth 32-key tile of the workgroup's run.
@@ -13,11 +14,12 @@
 //   * Each wave stages its own tiles (36 KB, one stage) by LDS-DMA: no barrier in
 //     the loop; while one wave computes, the others' tiles are in flight.
 //   * The four waves' (O, max, sum) are merged in LDS at the end of an item.
-// Workgroups take equal runs of the tile axis (attn_columns.h).  One query for
+// Workgroups take equal runs of the tile axis (attn_columns.h), short caches whole
+// items.  One query for
 // each of 16 caches of 4096..32768 keys (351 MB): 85 us a call against 119 us in
 // the many-row kernel, where 112 of a workgroup's 128 rows are idle and every
 // sequence has 16 splits, long or short; one sequence of 32768 keys: 52 us against
-// 65 us, of 512 keys: 21 us against 33 us.
+// 67 us, of 512 keys: 21 us against 33 us.
 #include <type_traits>
 
 #include "attn_columns.h"

@@ -369,6 +369,22 @@ def test_split_planner_few_rows():
     assert few_row_records(8, 32, 32, 64, 64, 1, 50000) == 1                 # 2048 items and more: never cut
 
 
+def test_counter_records_cover_the_included_headers():
+    """bench.py reports counter traffic only while the hash of a kernel's sources matches: the sources of every
+    kernel list each header that they include."""
+    import os
+    import re
+
+    import bench
+
+    for kernel, files in bench.KERNEL_SOURCES.items():
+        have = {os.path.basename(f) for f in files}
+        for f in files:
+            with open(os.path.join(bench.ROOT, f)) as fh:
+                want = set(re.findall(r'#include "([^"]+)"', fh.read()))
+            assert want <= have, (kernel, f, want - have)
+
+
 def test_split_planner_fp32():
     """fp32: split until there is about one workgroup per CU, at least 64 keys per split, at most 32."""
     assert planned_splits(1, 4, 2, 64, 64, 16, 528, dtype=1) == 8       # tiny: 2 workgroups, 528 keys
