@@ -13,10 +13,10 @@
 //   * the four waves' (O, max, sum) are merged in LDS at the end of an item.
 // Workgroups take equal runs of the tile axis (attn_columns.h), short caches whole
 // items.  One query for each of 16 paged caches of 8448..12544 keys, one layer of
-// the 8B shape (681 MB): TRACE; with set-up, tail and merge 131 us a call,
-// against 142 us in the many-row kernel with 4 splits a sequence; five sequences
-// of 20000 and 4 x 300 keys: 33 us against 47 us; one of 512 keys: 10 us against
-// 16, of 8192 keys: 16 us against 22.
+// the 8B shape: 131 us a call with the merge (every key read once: 683 MB by the
+// counters, 681 MB at least), against 142 us in the many-row kernel with 4 splits a
+// sequence; five sequences of 20000 and 4 x 300 keys: 33 us against 47 us; one of
+// 512 keys: 10 us against 16, of 8192 keys: 16 us against 22.
 #include <type_traits>
 
 #include "attn_columns.h"
