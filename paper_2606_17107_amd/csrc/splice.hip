@@ -62,7 +62,7 @@ constexpr int64_t kMaxGridX = 0xffffffffll / kBlock;   // blocks: HIP refuses 2^
 //   short segments, where a looping block has one or two tiles of its six: 0.36-0.88
 //     up to 1024 tokens (head size 64), 0.36-1.03 (128), 0.31-0.96 up to 512 (256);
 //   longer ones with tiles of 16 tokens (128 + 128 channels bf16, 64 + 64 fp32):
-//     lengths spread over a factor of four 0.78-1.06, all at the bound 0.98-1.08;
+//     lengths spread over a factor of four 0.67-1.06, all at the bound 0.88-1.12;
 //   longer ones, other tiles: up to 1.55 (head size 64, 16 x 3000 tokens: 239 against
 //     161 us), up to 1.28 (256).
 // An empty block costs 0.6 ns in the run form; the looping form's cost 0.9 ns, 1.7 ns
